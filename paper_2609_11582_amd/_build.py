@@ -40,7 +40,9 @@ EXTRA = {"decode_kernels.hip": ["-fno-honor-nans"], "dense_decode.hip": ["-fno-h
          "ladder_decode.hip": ["-fno-honor-nans"],
          # the codecs take window minima and maxima of finite directions (finite inputs are part of the device data
          # contract): no NaN quieting around them
-         "append_window.hip": ["-fno-honor-nans"], "codec_fused.hip": ["-fno-honor-nans"]}
+         "append_window.hip": ["-fno-honor-nans"], "codec_fused.hip": ["-fno-honor-nans"],
+         # row maxima of finite scores (and -inf where a key is masked)
+         "calib_kernels.hip": ["-fno-honor-nans"]}
 
 
 def build(verbose: bool = False, jobs: int = 4) -> str:

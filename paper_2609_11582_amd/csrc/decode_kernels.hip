@@ -218,15 +218,6 @@ template <int kMeta> constexpr int kMinOff = kMeta == kMetaMx ? kChSmall + 512 :
 // lane for fp16, two 4-byte loads for the 272 bytes of two MXFP4 records, none for TurboQuant keys)
 template <int kMeta> constexpr int kPairLoads = kMeta == kMetaFp16 ? 6 : kMeta == kMetaMx ? 7 : 5;
 
-// lane's 16 bytes at g go to LDS lds + 16 lane (lds wave-uniform, passed in m0; an LDS load needs
-// one wait state after m0 is written)
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
-  __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
-}
-// lane's 16 bytes at base + off go to LDS lds + 16 lane (base and lds wave-uniform)
-__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
-  __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
-}
 // lane's 4 bytes at g go to LDS lds + 4 lane
 __device__ __forceinline__ void dma4(const void* g, uint32_t lds) {
   __asm__ volatile("s_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(g), "{m0}"(lds) : "memory");

@@ -85,15 +85,15 @@ hipError_t launch_residual_store(const uint16_t* k_new, const uint16_t* v_new, i
                                  hipStream_t s);
 
 // Value-rotation calibration (Eq. 5): attention weights of up to 256 sequences per launch (the
-// workspace holds their row statistics), weighted covariance partials per (sequence, head, 64-token
-// chunk) and their reduction.
+// workspace holds their row statistics), weighted covariance partials per (sequence, head, run of
+// chunks) and their reduction.
 size_t calib_workspace_bytes(int B, int H, int Hq, int N);
 hipError_t launch_calib_weights(const uint16_t* q, const uint16_t* k, const LenArgs& lens, int b0, int nb, int N,
                                 int H, int Hq, float sm_scale, float* w, void* ws, hipStream_t s);
 hipError_t launch_calib_covariance(const uint16_t* v, const uint8_t* modality, const float* w, const LenArgs& lens,
                                    int b0, int nb, int N, int H, float* partial, int part0, float* cov, bool reduce,
                                    int nparts_total, hipStream_t s);
-constexpr int kCalibChunk = 64;  // tokens per covariance partial
+int calib_covariance_runs(int N);  // covariance partials per (sequence, KV head)
 
 struct CacheView {
   int B, H, Hq, cap;

@@ -41,6 +41,19 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
 
+// Direct memory-to-LDS loads, issued from inline assembly: the compiler's wait-count model makes every
+// LDS read wait for all of them, so a kernel that keeps some in flight counts its own (s_waitcnt
+// vmcnt) before it reads what they wrote.
+// lane's 16 bytes at g go to LDS lds + 16 lane (lds wave-uniform, passed in m0; an LDS load needs
+// one wait state after m0 is written)
+__device__ __forceinline__ void dma16(const void* g, uint32_t lds) {
+  __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "{m0}"(lds) : "memory");
+}
+// lane's 16 bytes at base + off go to LDS lds + 16 lane (base and lds wave-uniform)
+__device__ __forceinline__ void dma16s(const void* base, uint32_t off, uint32_t lds) {
+  __asm__ volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds) : "memory");
+}
+
 // MXFP4 key window metadata (OCP microscaling format: one E8M0 power-of-two scale per block of 32
 // values, FP4 E2M1 elements). Record of one window: bytes 4q..4q+1 hold the minimum's elements of
 // channels 4q..4q+3 (4 bits each), bytes 4q+2..4q+3 the step's, byte 128 + 2b the minimum's scale
