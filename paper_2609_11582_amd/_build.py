@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libokvq.so")
 SOURCES = ["api.hip", "codec_kernels.hip", "codec_fused.hip", "decode_kernels.hip", "calib_kernels.hip",
-           "dense_decode.hip", "ladder_codec.hip", "ladder_decode.hip", "append_window.hip"]
+           "dense_decode.hip", "ladder_codec.hip", "ladder_decode.hip", "append_window.hip", "codec_block.hip"]
 
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -41,6 +41,7 @@ EXTRA = {"decode_kernels.hip": ["-fno-honor-nans"], "dense_decode.hip": ["-fno-h
          # the codecs take window minima and maxima of finite directions (finite inputs are part of the device data
          # contract): no NaN quieting around them
          "append_window.hip": ["-fno-honor-nans"], "codec_fused.hip": ["-fno-honor-nans"],
+         "codec_block.hip": ["-fno-honor-nans"],
          # row maxima of finite scores (and -inf where a key is masked)
          "calib_kernels.hip": ["-fno-honor-nans"]}
 

@@ -98,6 +98,11 @@ Thresholds thresholds() {
   return Thresholds{cb.thr[0], cb.thr[1], cb.thr[2]};
 }
 
+// the positive half of the symmetric thresholds of a codebook (ascending; 1, 3 or 7 of them)
+void positive_thresholds(const Codebook& cb, float (&t)[7]) {
+  for (int i = cb.levels / 2; i + 1 < cb.levels; ++i) t[i - cb.levels / 2] = cb.thr[i];
+}
+
 bool aligned16(const void* p) { return p != nullptr && (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 okvq_status check_dims(const okvq_dims* d) {
@@ -300,6 +305,34 @@ okvq_status okvq_codebook_bits(int32_t bits, float* levels, float* thresholds_ou
   return OKVQ_OK;
 }
 
+// The block codec's arguments common to every call: sequences b0 .. b0 + nb - 1 of a block of n_rows rows
+static BlockArgs block_args(const okvq_dims& d, int32_t n_rows, int b0, int nb) {
+  BlockArgs a{};
+  a.th = thresholds();
+  if (is_ladder(&d)) {
+    positive_thresholds(codebook(d.key_bits), a.ktau);
+    positive_thresholds(codebook(d.value_bits), a.vtau);
+  }
+  a.n_rows = n_rows;
+  a.H = d.num_kv_heads;
+  a.cap = d.capacity;
+  a.b0 = b0;
+  a.nb = nb;
+  a.key_bits = d.key_bits;
+  a.value_bits = d.value_bits;
+  return a;
+}
+
+// Stateless lengths of the launch's sequences; returns the longest
+static int block_lens(BlockArgs& a, const int32_t* lens_host) {
+  int max_len = 0;
+  for (int i = 0; i < a.nb; ++i) {
+    a.lens.lens[i] = lens_host[a.b0 + i];
+    max_len = std::max(max_len, lens_host[a.b0 + i]);
+  }
+  return max_len;
+}
+
 static okvq_status quantize_keys_impl(const okvq_dims* dims, const uint16_t* k, int32_t n_tokens,
                                       const int32_t* lens_host, const int8_t* key_signs, uint8_t* k_codes,
                                       uint16_t* k_min, uint16_t* k_step, uint8_t* k_mx, uint16_t* k_norm,
@@ -309,55 +342,17 @@ static okvq_status quantize_keys_impl(const okvq_dims* dims, const uint16_t* k, 
     if (lens_host[b] > dims->capacity) return OKVQ_ERR_CAPACITY;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (is_ladder(dims)) {
-    const Codebook& cb = codebook(dims->key_bits);
-    for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
-      const int nb = std::min(kMaxLenArgs, dims->batch - b0);
-      LadderKeyArgs a{};
-      a.k = k;
-      a.n_rows = n_tokens;
-      a.H = dims->num_kv_heads;
-      a.cap = dims->capacity;
-      a.b0 = b0;
-      int max_len = 0;
-      for (int i = 0; i < nb; ++i) {
-        a.lens.lens[i] = lens_host[b0 + i];
-        max_len = std::max(max_len, lens_host[b0 + i]);
-      }
-      a.signs = key_signs;
-      a.k_codes = k_codes;
-      a.k_min = k_min;
-      a.k_step = k_step;
-      a.k_norm = k_norm;
-      for (int i = 0; i + 1 < cb.levels; ++i) a.tau[i] = cb.thr[i];
-      okvq_status st = hip_status(launch_ladder_keys(a, dims->key_bits, !is_fp16(dims), nb, max_len, s));
-      if (st != OKVQ_OK) return st;
-    }
-    return OKVQ_OK;
-  }
   for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
-    const int nb = std::min(kMaxLenArgs, dims->batch - b0);
-    CodecArgs a{};
-    a.j.src = k;
-    a.j.n_rows = n_tokens;
-    a.j.b0 = b0;
-    a.j.H = dims->num_kv_heads;
-    a.j.cap = dims->capacity;
-    int max_len = 0;
-    for (int i = 0; i < nb; ++i) {
-      a.j.lens.lens[i] = lens_host[b0 + i];
-      max_len = std::max(max_len, lens_host[b0 + i]);
-    }
-    plan_tiles(a, nb, max_len);
+    BlockArgs a = block_args(*dims, n_tokens, b0, std::min(kMaxLenArgs, dims->batch - b0));
+    const int max_len = block_lens(a, lens_host);
+    a.k = k;
     a.signs = key_signs;
     a.k_codes = k_codes;
     a.k_min = k_min;
     a.k_step = k_step;
     a.k_mx = k_mx;
     a.k_norm = k_norm;
-    a.key_meta = meta_mode(dims);
-    a.th = thresholds();
-    okvq_status st = hip_status(launch_codec(a, true, false, s));
+    okvq_status st = hip_status(launch_codec_block(a, meta_mode(dims), true, false, max_len, s));
     if (st != OKVQ_OK) return st;
   }
   return OKVQ_OK;
@@ -413,10 +408,22 @@ okvq_status okvq_quantize_values(const okvq_dims* dims, const uint16_t* v, const
     if (lens_host[b] > dims->capacity) return OKVQ_ERR_CAPACITY;
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (is_ladder(dims)) {
-    const Codebook& cb = codebook(dims->value_bits);
-    for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
-      const int nb = std::min(kMaxLenArgs, dims->batch - b0);
+  const bool exact = (flags & OKVQ_VALUE_EXACT) != 0;
+  for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
+    const int nb = std::min(kMaxLenArgs, dims->batch - b0);
+    int max_len = 0;
+    if (!exact) {
+      BlockArgs a = block_args(*dims, n_tokens, b0, nb);
+      max_len = block_lens(a, lens_host);
+      a.v = v;
+      a.modality = modality;
+      a.rot = v_rot;
+      a.v_codes = v_codes;
+      a.v_norm = v_norm;
+      a.global_rot = global_rot ? 1 : 0;
+      st = hip_status(launch_codec_block(a, meta_mode(dims), false, true, max_len, s));
+    } else if (is_ladder(dims)) {
+      const Codebook& cb = codebook(dims->value_bits);
       LadderValueArgs a{};
       a.v = v;
       a.modality = modality;
@@ -424,7 +431,6 @@ okvq_status okvq_quantize_values(const okvq_dims* dims, const uint16_t* v, const
       a.H = dims->num_kv_heads;
       a.cap = dims->capacity;
       a.b0 = b0;
-      int max_len = 0;
       for (int i = 0; i < nb; ++i) {
         a.lens.lens[i] = lens_host[b0 + i];
         max_len = std::max(max_len, lens_host[b0 + i]);
@@ -433,95 +439,92 @@ okvq_status okvq_quantize_values(const okvq_dims* dims, const uint16_t* v, const
       a.v_codes = v_codes;
       a.v_norm = v_norm;
       for (int i = 0; i + 1 < cb.levels; ++i) a.tau[i] = cb.thr[i];
-      st = hip_status(launch_ladder_values(a, dims->value_bits, (flags & OKVQ_VALUE_EXACT) != 0, nb, max_len, s));
-      if (st != OKVQ_OK) return st;
-    }
-    return OKVQ_OK;
-  }
-  const bool exact = (flags & OKVQ_VALUE_EXACT) != 0;
-  for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
-    const int nb = std::min(kMaxLenArgs, dims->batch - b0);
-    CodecArgs a{};
-    a.j.src = v;
-    a.j.msrc = modality;
-    a.j.global_rot = global_rot ? 1 : 0;
-    a.j.n_rows = n_tokens;
-    a.j.b0 = b0;
-    a.j.H = dims->num_kv_heads;
-    a.j.cap = dims->capacity;
-    int max_len = 0;
-    for (int i = 0; i < nb; ++i) {
-      a.j.lens.lens[i] = lens_host[b0 + i];
-      max_len = std::max(max_len, lens_host[b0 + i]);
-    }
-    if (exact) {
-      st = hip_status(launch_quantize_values_exact(a.j, nb, max_len, v_rot, thresholds(), v_codes, v_norm, nullptr, s));
+      st = hip_status(launch_ladder_values(a, dims->value_bits, nb, max_len, s));
     } else {
-      plan_tiles(a, nb, max_len);
-      a.vsrc = v;
-      a.rot = v_rot;
-      a.th = thresholds();
-      a.v_codes = v_codes;
-      a.v_norm = v_norm;
-      st = hip_status(launch_codec(a, false, true, s));
+      CodecJob j{};
+      j.src = v;
+      j.msrc = modality;
+      j.global_rot = global_rot ? 1 : 0;
+      j.n_rows = n_tokens;
+      j.b0 = b0;
+      j.H = dims->num_kv_heads;
+      j.cap = dims->capacity;
+      for (int i = 0; i < nb; ++i) {
+        j.lens.lens[i] = lens_host[b0 + i];
+        max_len = std::max(max_len, lens_host[b0 + i]);
+      }
+      st = hip_status(launch_quantize_values_exact(j, nb, max_len, v_rot, thresholds(), v_codes, v_norm, nullptr, s));
     }
     if (st != OKVQ_OK) return st;
   }
   return OKVQ_OK;
 }
 
-// Append to the bit-width ladder layout: the key codec (the method's keys requantize the open
-// window from the stage), the value codec of the new tokens, then the lengths advance.
+// The block codec's arguments of an append to sequences b0 .. b0 + nb - 1 of a cache
+static BlockArgs block_append_args(const okvq_cache* cache, const uint16_t* k_new, const uint16_t* v_new,
+                                   const uint8_t* mod_new, const int32_t* n_new_dev, int32_t n_max, uint32_t flags, int b0,
+                                   int nb) {
+  const okvq_dims& d = cache->dims;
+  BlockArgs a = block_args(d, n_max, b0, nb);
+  a.k = k_new;
+  a.v = v_new;
+  a.modality = mod_new;
+  a.begin_dev = cache->seq_lens;
+  a.count_dev = n_new_dev;
+  a.stage = (is_ladder(&d) && !is_fp16(&d)) ? nullptr : cache->k_stage;
+  a.signs = cache->key_signs;
+  a.k_codes = cache->k_codes;
+  a.k_min = is_fp16(&d) ? cache->k_min : nullptr;
+  a.k_step = is_fp16(&d) ? cache->k_step : nullptr;
+  a.k_mx = is_mx(&d) ? cache->k_mx : nullptr;
+  a.k_norm = cache->k_norm;
+  a.rotfrag = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(cache->v_rot16) + kRotInverseBytes);
+  a.v_codes = cache->v_codes;
+  a.v_norm = cache->v_norm;
+  a.mod_out = cache->modality;
+  a.k_res = d.residual ? cache->k_res : nullptr;
+  a.v_res = d.residual ? cache->v_res : nullptr;
+  a.global_rot = (flags & OKVQ_GLOBAL_ROTATION) ? 1 : 0;
+  return a;
+}
+
+// Append to the bit-width ladder layout: keys and values in one launch of the block codec (with exact-order
+// values, the keys alone and then the exact value codec), then the lengths.
 static okvq_status ladder_append(const okvq_cache* cache, const int32_t* lens_host, const uint16_t* k_new,
                                  const uint16_t* v_new, const uint8_t* mod_new, const int32_t* n_new_host,
                                  const int32_t* n_new_dev, int32_t n_max, bool exact, hipStream_t s) {
   const okvq_dims& d = cache->dims;
-  const bool tq = !is_fp16(&d);
-  const Codebook& kcb = codebook(d.key_bits);
-  const Codebook& vcb = codebook(d.value_bits);
   for (int b0 = 0; b0 < d.batch; b0 += kMaxLenArgs) {
     const int nb = std::min(kMaxLenArgs, d.batch - b0);
-    LadderKeyArgs ka{};
-    ka.k = k_new;
-    ka.n_rows = n_max;
-    ka.H = d.num_kv_heads;
-    ka.cap = d.capacity;
-    ka.b0 = b0;
-    ka.begin_dev = cache->seq_lens;
-    ka.count_dev = n_new_dev;
-    ka.stage = tq ? nullptr : cache->k_stage;
-    ka.signs = cache->key_signs;
-    ka.k_codes = cache->k_codes;
-    ka.k_min = tq ? nullptr : cache->k_min;
-    ka.k_step = tq ? nullptr : cache->k_step;
-    ka.k_norm = cache->k_norm;
-    for (int i = 0; i + 1 < kcb.levels; ++i) ka.tau[i] = kcb.thr[i];
-    LadderValueArgs va{};
-    va.v = v_new;
-    va.modality = mod_new;
-    va.n_rows = n_max;
-    va.H = d.num_kv_heads;
-    va.cap = d.capacity;
-    va.b0 = b0;
-    va.begin_dev = cache->seq_lens;
-    va.count_dev = n_new_dev;
-    va.mod_out = cache->modality;
-    va.rot = cache->v_rot;
-    va.v_codes = cache->v_codes;
-    va.v_norm = cache->v_norm;
-    for (int i = 0; i + 1 < vcb.levels; ++i) va.tau[i] = vcb.thr[i];
-    int key_span = 0, most = 0;
+    int span = 0, most = 0;  // tokens from the open window to the new end, appended tokens
     for (int i = 0; i < nb; ++i) {
-      const int L = lens_host[b0 + i], n = n_new_host[b0 + i];
-      if (n == 0) continue;
-      key_span = std::max(key_span, L + n - (tq ? L : (L / kW) * kW));
+      const int n = n_new_host[b0 + i];
+      if (n > 0) span = std::max(span, lens_host[b0 + i] % kW + n);
       most = std::max(most, n);
     }
     if (most == 0) continue;
-    okvq_status st = hip_status(launch_ladder_keys(ka, d.key_bits, tq, nb, key_span, s));
+    okvq_status st = hip_status(launch_codec_block(
+        block_append_args(cache, k_new, v_new, mod_new, n_new_dev, n_max, 0u, b0, nb), meta_mode(&d), true, !exact, span, s));
     if (st != OKVQ_OK) return st;
-    st = hip_status(launch_ladder_values(va, d.value_bits, exact, nb, most, s));
-    if (st != OKVQ_OK) return st;
+    if (exact) {
+      const Codebook& vcb = codebook(d.value_bits);
+      LadderValueArgs va{};
+      va.v = v_new;
+      va.modality = mod_new;
+      va.n_rows = n_max;
+      va.H = d.num_kv_heads;
+      va.cap = d.capacity;
+      va.b0 = b0;
+      va.begin_dev = cache->seq_lens;
+      va.count_dev = n_new_dev;
+      va.mod_out = cache->modality;
+      va.rot = cache->v_rot;
+      va.v_codes = cache->v_codes;
+      va.v_norm = cache->v_norm;
+      for (int i = 0; i + 1 < vcb.levels; ++i) va.tau[i] = vcb.thr[i];
+      st = hip_status(launch_ladder_values(va, d.value_bits, nb, most, s));
+      if (st != OKVQ_OK) return st;
+    }
     st = hip_status(launch_advance_lengths(cache->seq_lens + b0, n_new_dev + b0, nb, s));
     if (st != OKVQ_OK) return st;
   }
@@ -561,21 +564,24 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
                                                      exact, s)
                                      : OKVQ_OK;
   // Appends that touch few key windows per sequence take the window-parallel launch (codecs,
-  // residual rings and lengths in one launch); larger ones the tile launch, which streams longer
-  // spans at higher throughput. Both write the same bytes.
+  // residual rings and lengths in one launch); larger ones, and exact-order values, the block codec, whose
+  // throughput on long spans is higher. The tile codec writes the same bytes and runs where forced.
   int nwin = 0;  // key windows from the open window to the new end, largest over sequences
   for (int b = 0; b < d.batch; ++b) {
     const int L = lens_host[b], n = n_new_host[b];
     if (n > 0) nwin = std::max(nwin, (L + n + kW - 1) / kW - L / kW);
   }
   const int64_t nwg = (int64_t)nwin * d.num_kv_heads * d.batch;
-  bool window_path = !exact && !is_mx(&d) && (nwin <= 2 || (nwin <= kWindowPathMaxWindows && nwg <= kWindowPathMaxGroups));
-  if (const char* env = getenv("OKVQ_APPEND_PATH")) {  // "window" / "tile": force a path (tests, timing)
-    if (!strcmp(env, "tile")) window_path = false;
-    if (!strcmp(env, "window") && !exact && !is_mx(&d)) window_path = true;
+  enum { kPathWindow, kPathBlock, kPathTile } path = kPathBlock;
+  if (!exact && !is_mx(&d) && (nwin <= 2 || (nwin <= kWindowPathMaxWindows && nwg <= kWindowPathMaxGroups)))
+    path = kPathWindow;
+  if (const char* env = getenv("OKVQ_APPEND_PATH")) {  // force a path (tests, timing)
+    if (!strcmp(env, "tile") && !exact) path = kPathTile;
+    if (!strcmp(env, "block")) path = kPathBlock;
+    if (!strcmp(env, "window") && !exact && !is_mx(&d)) path = kPathWindow;
   }
-  if (events && d.residual && !window_path) return OKVQ_ERR_UNSUPPORTED;  // a second launch
-  if (d.residual && span > 0 && !window_path) {  // the fp16 rows, before the codec advances the lengths
+  if (events && d.residual && path != kPathWindow) return OKVQ_ERR_UNSUPPORTED;
+  if (d.residual && span > 0 && (path == kPathTile || exact)) {  // the fp16 rows, before the codec
     if ((int64_t)d.batch * d.num_kv_heads > INT32_MAX) return OKVQ_ERR_UNSUPPORTED;
     st = hip_status(launch_residual_store(k_new, v_new, n_max, cache->seq_lens, n_new_dev, d.batch, d.num_kv_heads,
                                           d.capacity, cache->k_res, cache->v_res, s));
@@ -583,6 +589,38 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
   }
   for (int b0 = 0; span > 0 && b0 < d.batch; b0 += kMaxLenArgs) {  // launches of up to 256 sequences
     const int nb = std::min(kMaxLenArgs, d.batch - b0);
+    int chunk_span = 0, chunk_nwin = 0;
+    for (int i = 0; i < nb; ++i) {
+      const int L = lens_host[b0 + i], n = n_new_host[b0 + i];
+      if (n == 0) continue;
+      chunk_span = std::max(chunk_span, L + n - (L / kW) * kW);
+      chunk_nwin = std::max(chunk_nwin, (L + n + kW - 1) / kW - L / kW);
+    }
+    if (chunk_span == 0) continue;
+    if (path == kPathBlock) {
+      BlockArgs a = block_append_args(cache, k_new, v_new, mod_new, n_new_dev, n_max, flags, b0, nb);
+      if (exact) a.k_res = a.v_res = nullptr;  // written above
+      st = hip_status(launch_codec_block(a, meta_mode(&d), true, !exact, chunk_span, s, events ? ev : nullptr));
+      if (st != OKVQ_OK) return st;
+      if (exact) {
+        CodecJob j{};
+        j.src = v_new;
+        j.msrc = mod_new;
+        j.global_rot = a.global_rot;
+        j.n_rows = n_max;
+        j.begin_dev = cache->seq_lens;
+        j.count_dev = n_new_dev;
+        j.b0 = b0;
+        j.H = d.num_kv_heads;
+        j.cap = d.capacity;
+        st = hip_status(launch_quantize_values_exact(j, nb, chunk_span, cache->v_rot, a.th, cache->v_codes, cache->v_norm,
+                                                     cache->modality, s));
+        if (st != OKVQ_OK) return st;
+      }
+      st = hip_status(launch_advance_lengths(cache->seq_lens + b0, n_new_dev + b0, nb, s));
+      if (st != OKVQ_OK) return st;
+      continue;
+    }
     CodecArgs a{};
     a.j.src = k_new;
     a.j.msrc = mod_new;
@@ -594,14 +632,10 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
     a.j.b0 = b0;
     a.j.H = d.num_kv_heads;
     a.j.cap = d.capacity;
-    int chunk_span = 0;
     for (int i = 0; i < nb; ++i) {
-      const int L = lens_host[b0 + i], n = n_new_host[b0 + i];
-      a.j.lens.lens[i] = L;
-      a.j.cnts.lens[i] = n;
-      if (n > 0) chunk_span = std::max(chunk_span, L + n - (L / 32) * 32);
+      a.j.lens.lens[i] = lens_host[b0 + i];
+      a.j.cnts.lens[i] = n_new_host[b0 + i];
     }
-    if (chunk_span == 0) continue;
     plan_tiles(a, nb, chunk_span);
     a.signs = cache->key_signs;
     a.k_codes = cache->k_codes;
@@ -614,34 +648,17 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
     a.v_codes = cache->v_codes;
     a.v_norm = cache->v_norm;
     a.mod_out = cache->modality;
-    if (exact) {
-      st = hip_status(launch_codec(a, true, false, s));
-      if (st != OKVQ_OK) return st;
-      CodecJob jv = a.j;
-      jv.src = v_new;
-      jv.stage = nullptr;
-      st = hip_status(launch_quantize_values_exact(jv, nb, chunk_span, cache->v_rot, a.th, cache->v_codes,
-                                                   cache->v_norm, cache->modality, s));
-      if (st != OKVQ_OK) return st;
-      st = hip_status(launch_advance_lengths(cache->seq_lens + b0, n_new_dev + b0, nb, s));
+    a.vsrc = v_new;
+    a.rotfrag = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(cache->v_rot16) + kRotInverseBytes);
+    a.seq_lens_out = cache->seq_lens;
+    a.ticket = reinterpret_cast<uint32_t*>(cache->seq_lens + d.batch);
+    a.status = cache->seq_lens + d.batch + 1;
+    if (path == kPathWindow) {
+      a.k_res = d.residual ? cache->k_res : nullptr;
+      a.v_res = d.residual ? cache->v_res : nullptr;
+      st = hip_status(launch_append_window(a, chunk_nwin, nb, s, events ? ev : nullptr));
     } else {
-      a.vsrc = v_new;
-      a.rotfrag = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(cache->v_rot16) + kRotInverseBytes);
-      a.seq_lens_out = cache->seq_lens;
-      a.ticket = reinterpret_cast<uint32_t*>(cache->seq_lens + d.batch);
-      a.status = cache->seq_lens + d.batch + 1;
-      if (window_path) {
-        a.k_res = d.residual ? cache->k_res : nullptr;
-        a.v_res = d.residual ? cache->v_res : nullptr;
-        int chunk_nwin = 0;
-        for (int i = 0; i < nb; ++i) {
-          const int L = lens_host[b0 + i], n = n_new_host[b0 + i];
-          if (n > 0) chunk_nwin = std::max(chunk_nwin, (L + n + kW - 1) / kW - L / kW);
-        }
-        st = hip_status(launch_append_window(a, chunk_nwin, nb, s, events ? ev : nullptr));
-      } else {
-        st = hip_status(launch_codec(a, true, true, s, events ? ev : nullptr));
-      }
+      st = hip_status(launch_codec(a, s, events ? ev : nullptr));
     }
     if (st != OKVQ_OK) return st;
   }

@@ -1,9 +1,11 @@
-// Key and value codecs of append and of the stateless MFMA-mode calls, in one persistent launch
-// (Sec. 2.1 Eq. 2 and Sec. 2.3 Eq. 4 for keys; Sec. 2.3 Eq. 6 with the codebook of Eq. 3 for
-// values).
+// Tile codec: key and value codecs of an append in one persistent launch of two waves per SIMD (Sec. 2.1
+// Eq. 2 and Sec. 2.3 Eq. 4 for keys; Sec. 2.3 Eq. 6 with the codebook of Eq. 3 for values). Appends take the
+// block codec (codec_block.hip) or the window-parallel launch (append_window.hip), which are faster at every
+// size measured (32768 tokens, 4 heads: 38.5 us here, 29.9 there); this one runs where OKVQ_APPEND_PATH=tile
+// forces it, as an independent implementation that their bytes are compared with.
 //
 // Work unit: a tile of 256 consecutive tokens of one (sequence, KV head), counted from the
-// sequence's first open window. A work-group has one or both of two roles, fixed per wave:
+// sequence's first open window. A work-group has two roles, fixed per wave:
 //  * key waves (4): wave k quantizes tokens [64 k, 64 k + 64) of the tile (key_quant.hpp);
 //  * value waves (4): phase 1 -- wave v loads the rows of tokens [64 v, 64 v + 64) straight into
 //    the work-group's LDS A tile and puts their fp16 norms, decision scales and per-modality
@@ -61,13 +63,8 @@ __device__ __forceinline__ TileCtx tile_from_hint(const CodecJob& j, int ntx, in
   c.bz = r / j.H;
   c.b = j.b0 + c.bz;
   c.seq = (size_t)c.b * j.H + c.h;
-  if (j.begin_dev) {
-    c.begin = j.lens.lens[c.bz];
-    c.len = c.begin + j.cnts.lens[c.bz];
-  } else {
-    c.begin = 0;
-    c.len = j.lens.lens[c.bz];
-  }
+  c.begin = j.lens.lens[c.bz];
+  c.len = c.begin + j.cnts.lens[c.bz];
   c.first = (c.begin / kW) * kW;
   c.tile0 = c.first + kTile * x;
   return c;
@@ -76,7 +73,6 @@ __device__ __forceinline__ TileCtx tile_from_hint(const CodecJob& j, int ntx, in
 // Append: the device lengths decide (clamped, so that values outside the contract stay memory
 // safe). Returns true where they differ from the host's copy the tile was planned with.
 __device__ __forceinline__ bool tile_check_device(const CodecJob& j, int ntx, int t, TileCtx& c) {
-  if (!j.begin_dev) return false;
   const int bd = min(max(j.begin_dev[c.b], 0), j.cap);
   const int ld = min(bd + min(max(j.count_dev[c.b], 0), j.n_rows), j.cap);
   if (bd == c.begin && ld == c.len) return false;
@@ -230,41 +226,20 @@ __device__ __forceinline__ void report_wait(const CodecArgs& a, bool arrived) {
 }
 
 // The wave's slice of R_m as B operands: bf[u][kk][part] for output block nb = 2 v + u, k-block kk,
-// part 0 = fp16(R) and 1 = fp16(R - fp16(R)). From the prepared fragments when there are any,
-// else converted here from the fp32 matrix.
+// part 0 = fp16(R) and 1 = fp16(R - fp16(R)), from the prepared fragments.
 __device__ __forceinline__ void load_rot_slice(const CodecArgs& a, int m, int v, uint4 (&bf)[2][4][2]) {
   const int lane = lane_id();
-  if (a.rotfrag) {
-    // uniform fragment base plus the lane's 16-byte offset (scalar base, one offset register)
-    const char* base = reinterpret_cast<const char*>(a.rotfrag) + (size_t)(m * 8 + 2 * v) * 8 * 1024;
-    uint32_t off = 16u * (uint32_t)lane;
-    __asm__ volatile("" : "+v"(off));  // computed here, not hoisted as 16 addresses held across the loop
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-        for (int part = 0; part < 2; ++part)
-          bf[u][kk][part] = *reinterpret_cast<const uint4*>(base + ((u * 4 + kk) * 2 + part) * 1024 + off);
-    return;
-  }
-  const int r = lane & 15, g = lane >> 4;
+  // uniform fragment base plus the lane's 16-byte offset (scalar base, one offset register)
+  const char* base = reinterpret_cast<const char*>(a.rotfrag) + (size_t)(m * 8 + 2 * v) * 8 * 1024;
+  uint32_t off = 16u * (uint32_t)lane;
+  __asm__ volatile("" : "+v"(off));  // computed here, not hoisted as 16 addresses held across the loop
 #pragma unroll
   for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const float4* p = reinterpret_cast<const float4*>(a.rot + ((size_t)(m * kD + 16 * (2 * v + u) + r)) * kD + 32 * kk + 8 * g);
-      const float4 f0 = p[0], f1 = p[1];
-      const float fv[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-      half8 hv, lv;
+    for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        hv[e] = (_Float16)fv[e];
-        lv[e] = (_Float16)(fv[e] - (float)hv[e]);
-      }
-      bf[u][kk][0] = __builtin_bit_cast(uint4, hv);
-      bf[u][kk][1] = __builtin_bit_cast(uint4, lv);
-    }
+      for (int part = 0; part < 2; ++part)
+        bf[u][kk][part] = *reinterpret_cast<const uint4*>(base + ((u * 4 + kk) * 2 + part) * 1024 + off);
 }
 
 // floor(x) as an integer in one instruction (v_cvt_flr_i32_f32)
@@ -351,7 +326,7 @@ __device__ __forceinline__ void value_role(const CodecArgs& a, int v, ValueShare
     uint4 bf[2][4][2];
     // the first modality's slice (video; R_0 with the global rotation), in flight during phase 1
     const int m_first = j.global_rot ? 0 : 1;
-    if (a.rotfrag) load_rot_slice(a, m_first, v, bf);
+    load_rot_slice(a, m_first, v, bf);
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint4 av[4][4];
 #pragma unroll
@@ -443,7 +418,7 @@ __device__ __forceinline__ void value_role(const CodecArgs& a, int v, ValueShare
       const int m = (mi == 0) ? m_first : (mi == 1 ? 1 - m_first : 2);  // video, audio, text (R_0 first if global)
       const uint32_t rbs = rbmask[m];
       if (rbs == 0) continue;
-      if (mi > 0 || !a.rotfrag) load_rot_slice(a, m, v, bf);
+      if (mi > 0) load_rot_slice(a, m, v, bf);
       // one window (row blocks 2 ww, 2 ww + 1): 32 MFMAs in four independent chains (two row blocks x
       // two output blocks, each over four k-blocks x hi, lo), then the codes; a row block without
       // the modality has an all-zero keep mask
@@ -486,19 +461,17 @@ __device__ __forceinline__ void value_role(const CodecArgs& a, int v, ValueShare
 }
 
 // ------------------------------------------------------------------------------------------------
-template <bool kKeys, bool kValues, int kMeta>
-__global__ __launch_bounds__(256 * (kKeys + kValues), (kKeys && kValues) ? 1 : 2) void k_codec(CodecArgs a) {
-  __shared__ __attribute__((aligned(16))) float key_lds[kKeys ? 4 * kKeyWaveLds : 4];
+template <int kMeta>
+__global__ __launch_bounds__(512, 1) void k_codec(CodecArgs a) {
+  __shared__ __attribute__((aligned(16))) float key_lds[4 * kKeyWaveLds];
   __shared__ __attribute__((aligned(16))) ValueShared vsh;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform for the compiler
-  if (kValues) {
-    if (threadIdx.x == 0) vsh.count = 0;
-    __syncthreads();  // the only work-group barrier; every wave reaches it
-  }
-  if (kKeys && wave < 4) {
+  if (threadIdx.x == 0) vsh.count = 0;
+  __syncthreads();  // the only work-group barrier before the tickets; every wave reaches it
+  if (wave < 4) {
     key_role<kMeta>(a, wave, key_lds + wave * kKeyWaveLds);
-  } else if (kValues) {
-    value_role(a, wave - (kKeys ? 4 : 0), vsh);
+  } else {
+    value_role(a, wave - 4, vsh);
   }
   if (a.ticket) {
     // Append: the lengths advance once every work-group has read them. Each work-group counts
@@ -550,8 +523,8 @@ void launch_one(Kernel fn, int grid, int block, hipStream_t s, hipEvent_t const*
     hipLaunchKernelGGL(fn, dim3(grid), dim3(block), 0, s, a);
 }
 
-hipError_t launch_codec(const CodecArgs& args, bool keys, bool values, hipStream_t s, hipEvent_t const* events) {
-  if (args.ntiles <= 0 || (!keys && !values)) return hipSuccess;
+hipError_t launch_codec(const CodecArgs& args, hipStream_t s, hipEvent_t const* events) {
+  if (args.ntiles <= 0) return hipSuccess;
   CodecArgs a = args;
   a.spin_limit = kSpinLimit;
   // test hook: a smaller bound for the value waves' wait (0 makes every wait give up at once)
@@ -561,27 +534,13 @@ hipError_t launch_codec(const CodecArgs& args, bool keys, bool values, hipStream
     int n = 0;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
   }
-  // resident work-groups: both roles fill a compute unit (8 waves at up to 256 VGPRs); one role
-  // leaves room for two
-  const int per_cu = (keys && values) ? 1 : 2;
-  const int grid = std::min(a.ntiles, per_cu * cus);
-  if (keys && values) {
-    if (a.key_meta == kMetaMx)
-      launch_one(k_codec<true, true, kMetaMx>, grid, 512, s, events, a);
-    else if (a.key_meta == kMetaTq)
-      launch_one(k_codec<true, true, kMetaTq>, grid, 512, s, events, a);
-    else
-      launch_one(k_codec<true, true, kMetaFp16>, grid, 512, s, events, a);
-  } else if (keys) {
-    if (a.key_meta == kMetaMx)
-      launch_one(k_codec<true, false, kMetaMx>, grid, 256, s, events, a);
-    else if (a.key_meta == kMetaTq)
-      launch_one(k_codec<true, false, kMetaTq>, grid, 256, s, events, a);
-    else
-      launch_one(k_codec<true, false, kMetaFp16>, grid, 256, s, events, a);
-  } else {
-    launch_one(k_codec<false, true, kMetaFp16>, grid, 256, s, events, a);
-  }
+  const int grid = std::min(a.ntiles, cus);  // resident work-groups: both roles fill a compute unit
+  if (a.key_meta == kMetaMx)
+    launch_one(k_codec<kMetaMx>, grid, 512, s, events, a);
+  else if (a.key_meta == kMetaTq)
+    launch_one(k_codec<kMetaTq>, grid, 512, s, events, a);
+  else
+    launch_one(k_codec<kMetaFp16>, grid, 512, s, events, a);
   return hipGetLastError();
 }
 

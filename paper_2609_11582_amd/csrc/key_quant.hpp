@@ -299,16 +299,4 @@ __device__ __forceinline__ void load_sign_words(const int8_t* signs, uint32_t (&
   for (int i = 0; i < 32; ++i) sw[i] = __builtin_amdgcn_readfirstlane(s[i]);
 }
 
-__device__ __forceinline__ void load_row_f16(const uint16_t* row, uint32_t (&raw)[64]) {
-  const uint4* p = reinterpret_cast<const uint4*>(row);
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const uint4 v = p[i];
-    raw[4 * i + 0] = v.x;
-    raw[4 * i + 1] = v.y;
-    raw[4 * i + 2] = v.z;
-    raw[4 * i + 3] = v.w;
-  }
-}
-
 }  // namespace okvq

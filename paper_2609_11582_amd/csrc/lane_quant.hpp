@@ -2,7 +2,7 @@
 // 8j + 7. The norm, the butterflies and the scaling run in the key codec's bit-exact order (the
 // halving tree, stages h = 1 .. 64, z = w fl(kappa / n16)); the levels and stages that pair a
 // channel with one 8 or more apart cross lanes by DPP. Used by the window-parallel append; the
-// bit-width ladder's key codec (four lanes per token) uses its DPP exchanges.
+// block codec (four lanes per token) uses its DPP exchanges and the MXFP4 metadata.
 #pragma once
 
 #include "key_quant.hpp"
@@ -97,6 +97,31 @@ __device__ __forceinline__ uint32_t lane_direction(uint4 kraw, uint2 sg, int j, 
 #pragma unroll
   for (int e = 0; e < 8; ++e) x[e] = x[e] * cinv;
   return n16;
+}
+
+// MXFP4 metadata of one channel of a window (thread = channel c, the 32 consecutive lanes of a block
+// together): the record's elements and scales are written where `live`, and (dequantized minimum,
+// 1 / dequantized step) returned, as the codes use them.
+__device__ __forceinline__ float2 mx_metadata(uint8_t* rec, int c, float lo, float step, bool live) {
+  auto block_max = [](float v) {  // over 32 consecutive lanes: DPP rotations of the row, then lane ^ 16
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x121, 0xf, 0xf, false)));
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x122, 0xf, 0xf, false)));
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x124, 0xf, 0xf, false)));
+    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x128, 0xf, 0xf, false)));
+    return fmaxf(v, __shfl_xor(v, 16));
+  };
+  const int em = mx_exponent(block_max(fabsf(lo))), es = mx_exponent(block_max(step));
+  const uint32_t cm = e2m1_encode(ldexpf(lo, -em)), cs = e2m1_encode(ldexpf(step, -es));
+  const int i = c & 3;
+  uint32_t word = (cm << (4 * i)) | (cs << (16 + 4 * i));  // the dword of the quad's four channels
+  word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0xB1, 0xf, 0xf, true);
+  word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0x4E, 0xf, 0xf, true);
+  if (live) {
+    if (i == 0) *reinterpret_cast<uint32_t*>(rec + c) = word;
+    if ((c & 31) == 0) *reinterpret_cast<uint16_t*>(rec + 128 + 2 * (c >> 5)) = (uint16_t)((em + 127) | ((es + 127) << 8));
+  }
+  const float sv = e2m1_decode(cs, es);
+  return make_float2(e2m1_decode(cm, em), (sv == 0.0f) ? 0.0f : div_rn(1.0f, sv));
 }
 
 }  // namespace okvq

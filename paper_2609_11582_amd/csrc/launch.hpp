@@ -9,11 +9,11 @@
 
 namespace okvq {
 
-// Where the codec kernels read token rows. Stateless calls (begin_dev == nullptr) quantize tokens
-// [0, lens[b - b0]) of a dense block. Append quantizes tokens [begin_dev[b], begin_dev[b] +
-// count_dev[b]) whose rows are src row (token - begin); older rows of the open key window come
-// from the fp16 stage. For append, lens / cnts hold the host's copy of the same lengths: the
-// kernels issue their row loads from them and then check the device values (which decide).
+// Where the tile codec and the exact-mode value kernel read token rows. Stateless calls (begin_dev ==
+// nullptr, exact-mode values only) quantize tokens [0, lens[b - b0]) of a dense block. Append quantizes
+// tokens [begin_dev[b], begin_dev[b] + count_dev[b]) whose rows are src row (token - begin); older rows of
+// the open key window come from the fp16 stage. For the tile codec lens / cnts hold the host's copy of
+// the same lengths: it issues its row loads from them and then checks the device values (which decide).
 struct CodecJob {
   const uint16_t* src;       // [B][H][n_rows][128] fp16
   const uint8_t* msrc;       // [B][n_rows] modality ids (values only)
@@ -38,7 +38,7 @@ constexpr int kRotFragments = 3 * 8 * 4 * 2;
 constexpr size_t kRotInverseBytes = 128 * 3 * 128 * 2;          // decode's inverse-rotation table
 constexpr size_t kRotFragmentBytes = (size_t)kRotFragments * 1024;
 
-// Arguments of the fused codec launch (keys, MFMA-mode values, or both) over tiles of 256 tokens.
+// Arguments of the fused tile codec launch (keys and MFMA-mode values of an append) over tiles of 256 tokens.
 struct CodecArgs {
   CodecJob j;
   int ntx;     // tiles per sequence (covering the longest span from a first open window)
@@ -53,12 +53,11 @@ struct CodecArgs {
   int key_meta;      // kMetaFp16, kMetaMx or kMetaTq (TurboQuant keys: codes against th, no metadata)
   // values
   const uint16_t* vsrc;  // value rows, laid out like j.src (the key rows)
-  const float* rot;      // fp32 R_m (used when rotfrag is null)
-  const uint4* rotfrag;  // prepared forward fragments, or null
+  const uint4* rotfrag;  // prepared forward fragments
   Thresholds th;
   uint8_t* v_codes;
   uint16_t* v_norm;
-  uint8_t* mod_out;  // append: the cache's modality map (written for KV head 0), else null
+  uint8_t* mod_out;  // the cache's modality map (written for KV head 0)
   // append: the last work-group to finish adds count_dev[b] to seq_lens[b] for the launch's
   // sequences; `ticket` counts finished work-groups and is returned to zero
   int32_t* seq_lens_out;
@@ -72,11 +71,47 @@ struct CodecArgs {
   uint16_t* v_res;
 };
 // events (optional): two events recorded at the start and end of the launch's execution
-hipError_t launch_codec(const CodecArgs& a, bool keys, bool values, hipStream_t s, hipEvent_t const* events = nullptr);
+hipError_t launch_codec(const CodecArgs& a, hipStream_t s, hipEvent_t const* events = nullptr);
 // Window-parallel append (MFMA-mode values; fp16 window metadata or TurboQuant keys): one launch
 // over nwin key windows per sequence from each open window, with the residual rings and the length
 // update (seq_lens_out, ticket as for the tile launch). Writes the tile codec's bytes.
 hipError_t launch_append_window(const CodecArgs& a, int nwin, int nb, hipStream_t s, hipEvent_t const* events = nullptr);
+
+// Block codec (codec_block.hip): keys, MFMA-mode values, or both, of up to 256 sequences, in the 2-bit layout
+// (key_bits = value_bits = 0) or the bit-width ladder. Stateless (begin_dev null): tokens [0, lens[i]) of a
+// dense block; append: tokens [begin_dev[b], begin_dev[b] + count_dev[b]), the device lengths deciding
+// (clamped into the buffers); launch_advance_lengths follows.
+struct BlockArgs {
+  const uint16_t* k;         // key rows [B][H][n_rows][128] fp16
+  const uint16_t* v;         // value rows, the same layout
+  const uint8_t* modality;   // [B][n_rows]
+  const int32_t* begin_dev;
+  const int32_t* count_dev;
+  uint16_t* stage;           // append: raw keys of the open window (null for the ladder's TurboQuant keys)
+  const int8_t* signs;
+  uint8_t* k_codes;
+  uint16_t* k_min;
+  uint16_t* k_step;
+  uint8_t* k_mx;
+  uint16_t* k_norm;
+  const float* rot;          // fp32 R_m (used when rotfrag is null)
+  const uint4* rotfrag;      // prepared forward fragments, or null
+  uint8_t* v_codes;
+  uint16_t* v_norm;
+  uint8_t* mod_out;          // append: the cache's modality map (written for KV head 0), else null
+  uint16_t* k_res;           // residual rings, or null
+  uint16_t* v_res;
+  Thresholds th;             // 2-bit layout
+  float ktau[7], vtau[7];    // ladder: the positive thresholds of the (symmetric) codebooks, ascending
+  int n_rows, H, cap, b0, nb, global_rot, key_bits, value_bits;
+  LenArgs lens;              // stateless
+  // set by the launcher
+  int key_nx, val_nx;
+  uint32_t key_units, paired;
+};
+// span: the most tokens from a sequence's first window to its end
+hipError_t launch_codec_block(const BlockArgs& a, int key_meta, bool keys, bool values, int span, hipStream_t s,
+                              hipEvent_t const* events = nullptr);
 hipError_t launch_prepare_fragments(const float* rot, uint4* frag, hipStream_t s);
 hipError_t launch_advance_lengths(int32_t* seq_lens, const int32_t* count, int B, hipStream_t s);
 // Residual rings: rows of the appended tokens among the last 128 of each sequence (device lengths).
@@ -163,26 +198,11 @@ hipError_t launch_decode_dense(const uint16_t* k, const uint16_t* v, const int32
                                int H, int Hq, int cap, float sm_scale, float* out, void* ws, const DensePlan& plan,
                                hipStream_t s, hipEvent_t const* events);
 
-// ---- bit-width ladder: b-bit keys and values (b = 2, 3, 4) in the token-major bit-stream layout ----
-// Stateless calls (begin_dev == nullptr): tokens [0, lens[b - b0]) of a dense block. Append:
-// tokens [begin_dev[b], begin_dev[b] + count_dev[b]) whose rows are row (token - begin) of the
-// block; the device lengths decide (clamped into the buffers) and the host's copy only sizes the
-// grid. The method's keys requantize the open window from `first` = 32 floor(begin / 32), its older
-// rows taken from the fp16 stage; TurboQuant keys and values are per token and start at begin.
-struct LadderKeyArgs {
-  const uint16_t* k;  // [B][H][n_rows][128] fp16
-  int n_rows, H, cap, b0;
-  LenArgs lens;
-  const int32_t* begin_dev;  // append: current lengths (device), else null
-  const int32_t* count_dev;  // append: appended tokens (device)
-  uint16_t* stage;           // append, method keys: [B][H][32][128] raw keys of the open window
-  const int8_t* signs;
-  uint8_t* k_codes;   // [B][H][cap][16 b]
-  uint16_t* k_min;    // [B][H][cap/32][128] fp16 (method keys)
-  uint16_t* k_step;
-  uint16_t* k_norm;   // [B][H][cap]
-  float tau[15];      // TurboQuant keys: the 2^b - 1 thresholds (fp32, ascending)
-};
+// ---- bit-width ladder: b-bit keys and values (b = 2, 3, 4) in the token-major bit-stream layout; the block
+// codec fills it, the exact-order values come from the kernel below. Stateless calls (begin_dev == nullptr):
+// tokens [0, lens[b - b0]) of a dense block. Append: tokens [begin_dev[b], begin_dev[b] + count_dev[b]) whose
+// rows are row (token - begin) of the block; the device lengths decide (clamped into the buffers) and the
+// host's copy only sizes the grid. ----
 struct LadderValueArgs {
   const uint16_t* v;  // [B][H][n_rows][128] fp16
   const uint8_t* modality;  // [B][n_rows]
@@ -196,11 +216,8 @@ struct LadderValueArgs {
   uint16_t* v_norm;
   float tau[15];
 };
-// max_len: the longest span of tokens from a tile start to the end (stateless: the longest length;
-// append: for the method's keys the longest length - first, else the most appended tokens)
-hipError_t launch_ladder_keys(const LadderKeyArgs& a, int bits, bool tq, int nb, int max_len, hipStream_t s);
-// exact: the sequential fp32 order (bit-exact codes); else the matrix cores (fp16 hi + lo split of R_m)
-hipError_t launch_ladder_values(const LadderValueArgs& a, int bits, bool exact, int nb, int max_len, hipStream_t s);
+// The sequential fp32 order (bit-exact codes). max_len: the longest length, or the most appended tokens
+hipError_t launch_ladder_values(const LadderValueArgs& a, int bits, int nb, int max_len, hipStream_t s);
 
 struct LadderDecodeArgs {
   const uint8_t* k_codes;

@@ -1,0 +1,42 @@
+"""The block codec (forced) against the tile codec (forced): every buffer of the cache byte for byte, for each
+key metadata format, over plans that end units of 64 and 128 tokens inside, at and just past their edges,
+start inside a window, leave a sequence empty, and use the residual rings and the single global rotation; one
+case has enough value units (at least 512 of 128 tokens) for the whole-size variant, the others take the
+half-size one. Both write the documented order's bytes, so nothing may differ."""
+
+import numpy as np
+import pytest
+
+from synth import gen_layer, workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _fill(path, monkeypatch, meta, lens, plan, heads, residual, flags):
+    import torch
+
+    import gpu_helpers as gh
+    import paper_2609_11582_amd as okvq
+    wl = workload("omni3b_b4_64k_stream")
+    lay = gen_layer(wl, 1, lengths=np.asarray(lens, np.int32), n_tokens=max(lens))
+    k, v = (np.concatenate([lay[f]] * heads, 1)[:, :heads].copy() for f in ("k", "v"))
+    monkeypatch.setenv("OKVQ_APPEND_PATH", path)
+    cap = (max(lens) + 31) // 32 * 32
+    cache = okvq.KVCache(len(lens), heads, heads, cap, torch.from_numpy(lay["signs"]), torch.from_numpy(lay["rot"]),
+                         key_meta=meta, residual=residual)
+    gh.append_chunks(cache, k, v, lay["modality"], lens, plan, flags=flags)
+    assert okvq.okvq_cache_status(cache) == 0
+    return {n: t.cpu().numpy() for n, t in cache.buffers.items()}
+
+
+@pytest.mark.parametrize("meta,residual,flags", [("fp16", 128, 0), ("fp16", 0, 2), ("mxfp4", 128, 0), ("turboquant", 0, 2)])
+@pytest.mark.parametrize("lens,plan,heads", [([1, 0, 33], [[1, 0, 33]], 1), ([64, 65, 127], [[64, 65, 127]], 2),
+                                             ([128, 129, 257], [[31, 1, 200], [97, 128, 57]], 1),
+                                             ([8300, 8129], [[8200, 8129], [100, 0]], 4)])
+def test_block_codec_writes_the_tile_codecs_bytes(meta, residual, flags, lens, plan, heads, monkeypatch):
+    print(f"[gpu-case] block codec {meta} residual={residual} flags={flags} lens={lens} plan={plan}", flush=True)
+    want = _fill("tile", monkeypatch, meta, lens, plan, heads, residual, flags)
+    got = _fill("block", monkeypatch, meta, lens, plan, heads, residual, flags)
+    for name in want:
+        a, b = got[name].view(np.uint8), want[name].view(np.uint8)
+        assert np.array_equal(a, b), f"{name}: {int((a != b).sum())} bytes differ"
