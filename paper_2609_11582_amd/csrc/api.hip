@@ -224,14 +224,14 @@ void jacobi_eigen(std::vector<double>& a, std::vector<double>& u, std::vector<do
   for (int i = 0; i < n; ++i) d[i] = a[(size_t)i * n + i];
 }
 
-// Tiles of 256 tokens covering `span` tokens from each sequence's first open window.
-// Appends take the window-parallel launch when they touch at most 2 key windows of a sequence (a
-// generation step), or at most 64 windows and 2048 work-groups in all (a streamed chunk); longer
-// spans take the tile launch, whose throughput is higher (32768-token prefill of 4 KV heads:
-// 43 us against 103 us).
-constexpr int kWindowPathMaxWindows = 64;
-constexpr int64_t kWindowPathMaxGroups = 2048;
+// Appends of at most this many key windows in all (over sequences and KV heads; two work-groups each) take
+// the window-parallel launch, larger ones the block codec and a launch for the lengths. The first has the
+// shorter chain but counts its work-groups one after another, 11.5 ns each. Device time of a call, window
+// against block: 4 windows (one token, 4 heads) 6.8 / 9.6 us, 128 windows 9.1-9.6 / 9.8-11.4, 256 windows 12.0-13.5
+// / 10.6-11.6, 512 windows 19.7 / 12.8.
+constexpr int64_t kWindowPathMaxGroups = 192;
 
+// Tiles of 256 tokens covering `span` tokens from each sequence's first open window (tile codec).
 void plan_tiles(CodecArgs& a, int nb, int span) {
   a.ntx = (span + 255) / 256;
   a.ntiles = a.ntx * a.j.H * nb;
@@ -563,9 +563,9 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
   if (is_ladder(&d)) return span > 0 ? ladder_append(cache, lens_host, k_new, v_new, mod_new, n_new_host, n_new_dev, n_max,
                                                      exact, s)
                                      : OKVQ_OK;
-  // Appends that touch few key windows per sequence take the window-parallel launch (codecs,
-  // residual rings and lengths in one launch); larger ones, and exact-order values, the block codec, whose
-  // throughput on long spans is higher. The tile codec writes the same bytes and runs where forced.
+  // Appends that touch few key windows take the window-parallel launch (codecs, residual rings and
+  // lengths in one launch); larger ones, and exact-order values, the block codec, whose throughput is
+  // higher. The tile codec writes the same bytes and runs where forced.
   int nwin = 0;  // key windows from the open window to the new end, largest over sequences
   for (int b = 0; b < d.batch; ++b) {
     const int L = lens_host[b], n = n_new_host[b];
@@ -573,14 +573,16 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
   }
   const int64_t nwg = (int64_t)nwin * d.num_kv_heads * d.batch;
   enum { kPathWindow, kPathBlock, kPathTile } path = kPathBlock;
-  if (!exact && !is_mx(&d) && (nwin <= 2 || (nwin <= kWindowPathMaxWindows && nwg <= kWindowPathMaxGroups)))
-    path = kPathWindow;
+  if (!exact && nwg <= kWindowPathMaxGroups) path = kPathWindow;
   if (const char* env = getenv("OKVQ_APPEND_PATH")) {  // force a path (tests, timing)
     if (!strcmp(env, "tile") && !exact) path = kPathTile;
     if (!strcmp(env, "block")) path = kPathBlock;
-    if (!strcmp(env, "window") && !exact && !is_mx(&d)) path = kPathWindow;
+    if (!strcmp(env, "window") && !exact) path = kPathWindow;
   }
-  if (events && d.residual && path != kPathWindow) return OKVQ_ERR_UNSUPPORTED;
+  // timed appends with the residual rings: those of few windows, in a format other than MXFP4
+  if (events && d.residual &&
+      (path == kPathTile || is_mx(&d) || (nwin > 2 && (nwin > 64 || nwg > 2048) && !getenv("OKVQ_APPEND_PATH"))))
+    return OKVQ_ERR_UNSUPPORTED;
   if (d.residual && span > 0 && (path == kPathTile || exact)) {  // the fp16 rows, before the codec
     if ((int64_t)d.batch * d.num_kv_heads > INT32_MAX) return OKVQ_ERR_UNSUPPORTED;
     st = hip_status(launch_residual_store(k_new, v_new, n_max, cache->seq_lens, n_new_dev, d.batch, d.num_kv_heads,

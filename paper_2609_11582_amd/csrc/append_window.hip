@@ -20,7 +20,7 @@
 // Older tokens of the open window come from the key stage; their key codes are rewritten with the
 // window's new minimum and step, their value codes are kept. The work-group of the first window, the
 // only one that reads the stage, rewrites it with the raw rows of the new open window after a
-// barrier that follows its reads. The last work-group to finish advances the lengths.
+// barrier that follows its reads. The work-group with the last ticket advances the lengths.
 #include <hip/hip_ext.h>
 
 #include "lane_quant.hpp"
@@ -60,6 +60,7 @@ struct WindowArgs {
   uint8_t* k_codes;
   uint16_t* k_min;
   uint16_t* k_step;
+  uint8_t* k_mx;
   uint16_t* k_norm;
   const uint4* rotfrag;      // prepared forward fragments of R_m
   uint8_t* v_codes;
@@ -133,11 +134,21 @@ __device__ __forceinline__ void value_inputs(const WindowArgs& a, size_t seq, in
   wmod = wfresh ? wm : 3u;
 }
 
+// The work-group's ticket, taken by its last thread: by then the lengths are in registers, so the work-group
+// that takes the last one may advance them. Taken where the row loads have been consumed, so that the
+// counter's round trip (and its turn: 11.5 ns a work-group, one after another) runs beside the rest of
+// the codes instead of after them.
+__device__ __forceinline__ void take_ticket(const WindowArgs& a, int tid, uint32_t& ticket) {
+  uint32_t* p = a.ticket;
+  __asm__ volatile("" : "+v"(p));  // per lane: of a uniform counter the compiler makes a wave-wide sum, and waits for it
+  if (tid == kThreads - 1) ticket = __hip_atomic_fetch_add(p, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // The key work-group of a window: directions, window statistics, codes, norms, the stage and the
 // key ring of the residual.
 template <int kMeta>
 __device__ __forceinline__ void key_window(const WindowArgs& a, WindowShared& sh, size_t seq, int begin, int len,
-                                           int wi, int tid) {
+                                           int wi, int tid, uint32_t& ticket) {
   const WindowArgs& J = a;
   const int t = tid >> 4, j = tid & 15;
   const int first = (begin / kW) * kW, w0 = first + kW * wi, tok = w0 + t;
@@ -157,7 +168,7 @@ __device__ __forceinline__ void key_window(const WindowArgs& a, WindowShared& sh
   if (a.k_res && fresh && tok >= len - kResidual)  // the residual ring: raw rows of the last 128 tokens
     reinterpret_cast<uint4*>(a.k_res + (seq * kResidual + (tok & (kResidual - 1))) * kD)[j] = kraw;
   // ---- window minimum / maximum per channel: LDS atomics of the valid tokens ----
-  if constexpr (kMeta == kMetaFp16) {
+  if constexpr (kMeta != kMetaTq) {
     if (valid) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -168,19 +179,24 @@ __device__ __forceinline__ void key_window(const WindowArgs& a, WindowShared& sh
   }
   if (restage) __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this thread's stage reads have landed
   __syncthreads();  // B1: window extremes written; every stage read has landed
+  take_ticket(a, tid, ticket);
   if (restage && stok >= begin && stok < len)  // the new open window's raw keys
     reinterpret_cast<uint4*>(J.stage + (seq * kW + t) * kD)[j] = select4(open == first, kraw, sraw);
   const size_t nw = J.cap / kW;
   const int gwin = w0 / kW;
-  if constexpr (kMeta == kMetaFp16) {
-    if (tid < kD) {
+  if constexpr (kMeta != kMetaTq) {
+    if (tid < kD) {  // two whole waves
       const float l = sh.kmin[tid + (tid >> 3)] + 0.0f;  // canonical +0
       const float u = sh.kmax[tid + (tid >> 3)] + 0.0f;
       const float step = div_rn(u - l, 3.0f);
-      const uint32_t m16 = f2h(l), s16 = f2h(step);
-      a.k_min[(seq * nw + gwin) * kD + tid] = (uint16_t)m16;
-      a.k_step[(seq * nw + gwin) * kD + tid] = (uint16_t)s16;
-      sh.kstat[tid] = make_float2(h2f(m16), (s16 == 0) ? 0.0f : div_rn(1.0f, h2f(s16)));
+      if constexpr (kMeta == kMetaMx) {
+        sh.kstat[tid] = mx_metadata(a.k_mx + (seq * nw + gwin) * kMxRecord, tid, l, step, true);
+      } else {
+        const uint32_t m16 = f2h(l), s16 = f2h(step);
+        a.k_min[(seq * nw + gwin) * kD + tid] = (uint16_t)m16;
+        a.k_step[(seq * nw + gwin) * kD + tid] = (uint16_t)s16;
+        sh.kstat[tid] = make_float2(h2f(m16), (s16 == 0) ? 0.0f : div_rn(1.0f, h2f(s16)));
+      }
     }
     __syncthreads();  // B2: window statistics
   }
@@ -192,7 +208,7 @@ __device__ __forceinline__ void key_window(const WindowArgs& a, WindowShared& sh
     for (int i = 0; i < 4; ++i) {
       const int sh2 = 2 * (4 * (j & 1) + i);
       uint32_t c0, c1;
-      if constexpr (kMeta == kMetaFp16) {
+      if constexpr (kMeta != kMetaTq) {
         const float4 st = *reinterpret_cast<const float4*>(&sh.kstat[8 * j + 2 * i]);
         constexpr float kRound = 8388608.0f;  // 2^23: rint of the clamped value in the low bits
         const float t0 = (x[2 * i] - st.x) * st.y;
@@ -218,7 +234,7 @@ __device__ __forceinline__ void key_window(const WindowArgs& a, WindowShared& sh
 // 16w + 15 of the 32 tokens on the matrix cores, per present modality, and writes their code bytes;
 // also the modality map and the value ring of the residual.
 __device__ __forceinline__ void value_window(const WindowArgs& a, WindowShared& sh, size_t seq, int b, int h,
-                                             int begin, int len, int wi, int tid) {
+                                             int begin, int len, int wi, int tid, uint32_t& ticket) {
   const WindowArgs& J = a;
   const int t = tid >> 4, j = tid & 15, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -265,6 +281,7 @@ __device__ __forceinline__ void value_window(const WindowArgs& a, WindowShared& 
   if (a.v_res && fresh && tok >= len - kResidual)  // the residual ring: raw rows of the last 128 tokens
     reinterpret_cast<uint4*>(a.v_res + (seq * kResidual + (tok & (kResidual - 1))) * kD)[j] = vraw;
   __syncthreads();  // B1: A tile and token tables written
+  take_ticket(a, tid, ticket);
   const int g = lane >> 4;
   const uint32_t tm = sh.tmod[lane & 31];
   uint32_t vb[2] = {0u, 0u};
@@ -317,7 +334,6 @@ __device__ __forceinline__ void value_window(const WindowArgs& a, WindowShared& 
 // of window x - nwin.
 template <int kMeta>
 __global__ __launch_bounds__(kThreads) void k_append_window(WindowArgs a) {
-  static_assert(kMeta == kMetaFp16 || kMeta == kMetaTq, "fp16 window metadata or TurboQuant keys");
   __shared__ WindowShared sh;
   const WindowArgs& J = a;
   const int tid = threadIdx.x;
@@ -328,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void k_append_window(WindowArgs a) {
   // the device lengths decide, clamped into the buffers (the host's copy planned the grid)
   const int begin = min(max(J.begin_dev[b], 0), J.cap);
   const int len = min(begin + min(max(J.count_dev[b], 0), J.n_rows), J.cap);
-  if (kMeta == kMetaFp16 && !values) {
+  if (kMeta != kMetaTq && !values) {
     if (tid < kStatSlots) {
       sh.kmin[tid] = __builtin_inff();
       sh.kmax[tid] = -__builtin_inff();
@@ -336,20 +352,21 @@ __global__ __launch_bounds__(kThreads) void k_append_window(WindowArgs a) {
     __syncthreads();  // B0 (the waves of a work-group start together)
   }
   const int w0 = (begin / kW) * kW + kW * wi;  // the work-group's window
-  if (len > begin && w0 < len) {               // uniform
+  // the lengths are in registers from here on (and are not read again): the ticket may be taken
+  __asm__ volatile("" ::"s"(begin), "s"(len) : "memory");
+  uint32_t ticket;  // of the last thread only (no other value is joined with it, so nothing waits for it here)
+  if (len > begin && w0 < len) {  // uniform
     if (values)
-      value_window(a, sh, seq, b, h, begin, len, wi, tid);
+      value_window(a, sh, seq, b, h, begin, len, wi, tid, ticket);
     else
-      key_window<kMeta>(a, sh, seq, begin, len, wi, tid);
+      key_window<kMeta>(a, sh, seq, begin, len, wi, tid, ticket);
+  } else {
+    take_ticket(a, tid, ticket);
   }
 
-  // The lengths advance once every work-group has read them: each work-group counts itself after
-  // all its threads are done; the last one writes the new lengths and clears the counter.
-  __syncthreads();
-  if (tid == 0) {
-    const uint32_t total = gridDim.x * gridDim.y * gridDim.z;
-    sh.last = (__hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total - 1) ? 1u : 0u;
-  }
+  // The lengths advance once every work-group has read them, i.e. in the work-group with the last ticket,
+  // which writes the new lengths and clears the counter.
+  if (tid == kThreads - 1) sh.last = ticket == gridDim.x * gridDim.y * gridDim.z - 1 ? 1u : 0u;
   __syncthreads();
   if (sh.last) {
     // The counts are read only here: vector reads of the lengths' cache line at the start of every
@@ -375,6 +392,7 @@ hipError_t launch_append_window(const CodecArgs& c, int nwin, int nb, hipStream_
   a.k_codes = c.k_codes;
   a.k_min = c.k_min;
   a.k_step = c.k_step;
+  a.k_mx = c.k_mx;
   a.k_norm = c.k_norm;
   a.rotfrag = c.rotfrag;
   a.v_codes = c.v_codes;
@@ -392,8 +410,9 @@ hipError_t launch_append_window(const CodecArgs& c, int nwin, int nb, hipStream_
   a.global_rot = c.j.global_rot;
   const int key_meta = c.key_meta;
   const dim3 grid(2 * nwin, a.H, nb);
-  if (key_meta != kMetaTq && key_meta != kMetaFp16) return hipErrorInvalidValue;
-  void (*fn)(WindowArgs) = key_meta == kMetaTq ? k_append_window<kMetaTq> : k_append_window<kMetaFp16>;
+  void (*fn)(WindowArgs) = key_meta == kMetaTq   ? k_append_window<kMetaTq>
+                           : key_meta == kMetaMx ? k_append_window<kMetaMx>
+                                                 : k_append_window<kMetaFp16>;
   if (events)
     hipExtLaunchKernelGGL(fn, grid, dim3(kThreads), 0, s, events[0], events[1], 0, a);
   else

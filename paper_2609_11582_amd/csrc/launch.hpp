@@ -72,7 +72,7 @@ struct CodecArgs {
 };
 // events (optional): two events recorded at the start and end of the launch's execution
 hipError_t launch_codec(const CodecArgs& a, hipStream_t s, hipEvent_t const* events = nullptr);
-// Window-parallel append (MFMA-mode values; fp16 window metadata or TurboQuant keys): one launch
+// Window-parallel append (MFMA-mode values): one launch
 // over nwin key windows per sequence from each open window, with the residual rings and the length
 // update (seq_lens_out, ticket as for the tile launch). Writes the tile codec's bytes.
 hipError_t launch_append_window(const CodecArgs& a, int nwin, int nb, hipStream_t s, hipEvent_t const* events = nullptr);

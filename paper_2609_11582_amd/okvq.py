@@ -263,7 +263,7 @@ def okvq_append(cache: "KVCache", lens, k_new, v_new, mod_new, n_new, n_new_dev,
 def okvq_append_timed(cache: "KVCache", lens, k_new, v_new, mod_new, n_new, n_new_dev, n_max, events, flags=0,
                       stream=None, check=True) -> int:
     """okvq_append that records two torch.cuda.Event objects at the start and end of its codec
-    launch (the window-parallel launch, or the fused codec launch)."""
+    launch (the window-parallel launch, or the block codec's)."""
     B, H = cache.dims.batch, cache.dims.num_kv_heads
     _need_len(lens, B, "lens")
     _need_len(n_new, B, "n_new")

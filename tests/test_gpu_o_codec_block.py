@@ -1,4 +1,4 @@
-"""The block codec (forced) against the tile codec (forced): every buffer of the cache byte for byte, for each
+"""The block codec and the window-parallel append (forced) against the tile codec (forced): every buffer of the cache byte for byte, for each
 key metadata format, over plans that end units of 64 and 128 tokens inside, at and just past their edges,
 start inside a window, leave a sequence empty, and use the residual rings and the single global rotation; one
 case has enough value units (at least 512 of 128 tokens) for the whole-size variant, the others take the
@@ -33,10 +33,11 @@ def _fill(path, monkeypatch, meta, lens, plan, heads, residual, flags):
 @pytest.mark.parametrize("lens,plan,heads", [([1, 0, 33], [[1, 0, 33]], 1), ([64, 65, 127], [[64, 65, 127]], 2),
                                              ([128, 129, 257], [[31, 1, 200], [97, 128, 57]], 1),
                                              ([8300, 8129], [[8200, 8129], [100, 0]], 4)])
-def test_block_codec_writes_the_tile_codecs_bytes(meta, residual, flags, lens, plan, heads, monkeypatch):
+def test_block_and_window_codecs_write_the_tile_codecs_bytes(meta, residual, flags, lens, plan, heads, monkeypatch):
     print(f"[gpu-case] block codec {meta} residual={residual} flags={flags} lens={lens} plan={plan}", flush=True)
     want = _fill("tile", monkeypatch, meta, lens, plan, heads, residual, flags)
-    got = _fill("block", monkeypatch, meta, lens, plan, heads, residual, flags)
-    for name in want:
-        a, b = got[name].view(np.uint8), want[name].view(np.uint8)
-        assert np.array_equal(a, b), f"{name}: {int((a != b).sum())} bytes differ"
+    for path in ("block", "window"):
+        got = _fill(path, monkeypatch, meta, lens, plan, heads, residual, flags)
+        for name in want:
+            a, b = got[name].view(np.uint8), want[name].view(np.uint8)
+            assert np.array_equal(a, b), f"{path}, {name}: {int((a != b).sum())} bytes differ"
