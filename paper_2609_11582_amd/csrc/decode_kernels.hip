@@ -7,7 +7,7 @@
 // split's per-modality accumulators are un-rotated on MFMA (the inverse rotation is linear, so
 // applying it per split and then merging equals applying it once per modality after aggregation,
 // Sec. 2.3) and one normalized partial output per split is written. k_decode_merge combines the
-// splits by log-sum-exp.
+// splits by log-sum-exp; a plan of one split per sequence writes the outputs itself and needs no merge.
 //
 // What one wave does per window pair (all G <= 8 query heads of the KV head from one read):
 //  * scores in the rotated key space (Sec. 2.3): s_i = n_i (q'.m_g + sum_c q'_c step_gc code_ic),
@@ -49,6 +49,10 @@ constexpr int kDecWaves = 8;                    // waves per split work-group
 constexpr int kATile = 3 * kD + 8;              // fp16 row pitch of the un-rotation A tile
 constexpr int kAccPitch = 28;                   // combine tile [channel][24 rows + 4]: conflict-free b128
 constexpr int kMinWps = 2 * kDecWaves;          // fewest windows per split (a pair per wave)
+// Sequences of at most this many windows take one split, whose work-group writes the output rows itself: a
+// second window pair per wave costs less than the merge launch (1024 tokens 11.8 -> 10.4 us, 512 tokens
+// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8).
+constexpr int kOneSplitWins = 32;
 constexpr float kLazy = 8.0f;                   // log2 headroom of the lazily updated softmax max
 
 struct DecodeArgs {
@@ -64,7 +68,7 @@ struct DecodeArgs {
   const int8_t* signs;
   const uint16_t* q;
   const uint16_t* rot16t;  // [128][3][128] fp16: (c, m, k) -> R_m[k][c]
-  float* ws;               // partial records [B][H][nsplit][kRecFloats]
+  float* ws;               // partial records [B][H][nsplit][kRecFloats], or (kOne) the output rows [B][Hq][128]
   int H, Hq, G, cap, wps, nsplit;
   int residual;      // tokens at the end of each sequence left to the merge launch (fp16 residual)
   float qscale;      // sm_scale * log2(e) / sqrt(128)
@@ -312,7 +316,9 @@ __device__ __forceinline__ half8 key_a_lut(const uint2* vlut, uint2 w, int kk) {
 
 // kGlobal: every value was rotated by R_0 (the single global rotation): one accumulator set whose
 // rows 0-7 sum window A's tokens and rows 8-15 window B's, no modality masks, one un-rotation
-template <int kMeta, bool kGlobal>
+// kOne: one split per sequence, which writes the output rows instead of a record (a template argument: as a
+// run-time branch it slowed the other plans by up to 2 %)
+template <int kMeta, bool kGlobal, bool kOne>
 __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   constexpr bool kMx = kMeta == kMetaMx;
   constexpr bool kTq = kMeta == kMetaTq;
@@ -337,7 +343,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform (scalar) for the compiler
   const int col = lane & 15, g = lane >> 4, hd = col & 7, side = col >> 3, c7 = col & 7;
   const size_t seq = (size_t)b * p.H + h;
-  float* rec = p.ws + (seq * p.nsplit + split) * kRecFloats;
+  float* rec = p.ws + (kOne ? ((size_t)b * p.Hq + h * p.G) * kD : (seq * p.nsplit + split) * kRecFloats);
   const int w_begin = split * p.wps;
   const int w_plan = min(w_begin + p.wps, p.cap / kW);  // windows of this split by the plan
   const int wA0 = w_begin + 2 * wave;                    // this wave's pairs: (wA0 + 16 k, +1)
@@ -385,7 +391,10 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   const int w_end = min(w_plan, nwin);
   if (w_begin >= w_end) {  // empty split (ragged batch): a header the merge skips
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no ring load may land after the exit
-    write_empty_record(rec, tid);
+    if constexpr (kOne)
+      write_empty_rows(rec, p.G, tid);
+    else
+      write_empty_record(rec, tid);
     return;
   }
 
@@ -828,7 +837,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
     const float sc = (hh < p.G && L > 0.0f) ? ldexpf(1.0f / L, e) : 0.0f;
     // the wave's accumulators carry its operand scale 2^E_w
     fac[hh][w] = (mv[w] == -__builtin_inff()) ? 0.0f : fast_exp2(mv[w] - M - (float)wexp[w]) * sc;
-    if (w == 0) {
+    if (w == 0 && !kOne) {
       rec[hh] = M;
       rec[8 + hh] = L;
     }
@@ -887,11 +896,22 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   }
   if (lane < 32) {
     const float sc = ldexpf(1.0f, -e);
+    if constexpr (!kOne) {
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
+      for (int cb = 0; cb < 2; ++cb) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        rec[kRecHeader + (4 * (lane >> 4) + i) * kD + 32 * wave + 16 * cb + (lane & 15)] = dacc[cb][i] * sc;
+        for (int i = 0; i < 4; ++i)
+          rec[kRecHeader + (4 * (lane >> 4) + i) * kD + 32 * wave + 16 * cb + (lane & 15)] = dacc[cb][i] * sc;
+      }
+    } else {  // the output rows of the G heads
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int hh = 4 * (lane >> 4) + i;
+        if (hh < p.G) {
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) rec[hh * kD + 32 * wave + 16 * cb + (lane & 15)] = dacc[cb][i] * sc;
+        }
+      }
     }
   }
 }
@@ -1288,6 +1308,7 @@ DecodePlan plan_decode(int B, int H, int max_len) {
   long target_groups = 256;  // one work-group per compute unit
   if (const char* env = getenv("OKVQ_DECODE_GROUPS")) target_groups = std::max(1L, atol(env));
   int wps = (int)((nwin * units + target_groups - 1) / target_groups);
+  if (nwin <= kOneSplitWins) wps = std::max(wps, nwin);
   wps = std::max(wps, kMinWps);
   wps = std::max(wps, (nwin + kMaxSplits - 1) / kMaxSplits);
   wps = (wps + 1) / 2 * 2;  // whole window pairs
@@ -1304,6 +1325,17 @@ static size_t record_bytes(int B, int H, int max_len) {
 }
 
 size_t decode_workspace_bytes(int B, int H, int /*Hq*/, int max_len) { return record_bytes(B, H, max_len); }
+
+template <bool kOne>
+static auto pick_decode(int meta, bool global_rot) -> void (*)(DecodeArgs) {
+  if (global_rot)
+    return meta == kMetaMx   ? k_decode<kMetaMx, true, kOne>
+           : meta == kMetaTq ? k_decode<kMetaTq, true, kOne>
+                             : k_decode<kMetaFp16, true, kOne>;
+  return meta == kMetaMx   ? k_decode<kMetaMx, false, kOne>
+         : meta == kMetaTq ? k_decode<kMetaTq, false, kOne>
+                           : k_decode<kMetaFp16, false, kOne>;
+}
 
 hipError_t launch_decode(const CacheView& c, const uint16_t* q, float sm_scale, float* out, void* ws,
                          const DecodePlan& plan, hipStream_t s, uint32_t cb01, uint32_t cb23, int /*max_len*/,
@@ -1330,22 +1362,19 @@ hipError_t launch_decode(const CacheView& c, const uint16_t* q, float sm_scale, 
   a.wps = plan.wins_per_split;
   a.nsplit = plan.nsplit;
   a.residual = c.residual;
+  const bool one = plan.nsplit == 1 && !c.residual && !events;  // the only split writes the outputs itself
+  if (one) a.ws = out;
   a.qscale = sm_scale * 1.4426950408889634f * 0.08838834764831845f;
   a.cb01 = cb01;
   a.cb23 = cb23;
   hipError_t e;
   const dim3 grid(plan.nsplit, c.H, c.B), block(64 * kDecWaves);
-  auto kern = global_rot ? (c.key_meta == kMetaMx   ? k_decode<kMetaMx, true>
-                            : c.key_meta == kMetaTq ? k_decode<kMetaTq, true>
-                                                    : k_decode<kMetaFp16, true>)
-                         : (c.key_meta == kMetaMx   ? k_decode<kMetaMx, false>
-                            : c.key_meta == kMetaTq ? k_decode<kMetaTq, false>
-                                                    : k_decode<kMetaFp16, false>);
+  auto kern = one ? pick_decode<true>(c.key_meta, global_rot) : pick_decode<false>(c.key_meta, global_rot);
   if (events)  // events bound to the two dispatches: start and end of each kernel's execution
     hipExtLaunchKernelGGL(kern, grid, block, 0, s, events[0], events[1], 0, a);
   else
     hipLaunchKernelGGL(kern, grid, block, 0, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = hipGetLastError()) != hipSuccess || one) return e;
   const dim3 mgrid(c.Hq, c.B), mblock(kMergeThreads);
   if (c.residual) {
     TailArgs t;

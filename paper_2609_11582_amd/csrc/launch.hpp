@@ -168,6 +168,12 @@ __device__ __forceinline__ void write_empty_record(float* rec, int tid) {
   if (tid < 8 * kD / 4) reinterpret_cast<float4*>(rec + kRecHeader)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
+// Output rows of a sequence with no tokens where the only split writes them itself: zeros for the G heads
+// of the KV head. Threads tid < 256 of the work-group call it.
+__device__ __forceinline__ void write_empty_rows(float* rows, int G, int tid) {
+  if (tid < G * kD / 4) reinterpret_cast<float4*>(rows)[tid] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
+
 struct DecodePlan {
   int wins_per_split;  // 32-token windows per split-K work-group
   int nsplit;          // splits per (sequence, KV head)
@@ -231,7 +237,7 @@ struct LadderDecodeArgs {
   const int8_t* signs;
   const uint16_t* q;
   const uint16_t* rot16t;
-  float* ws;
+  float* ws;               // partial records, or (one split per sequence, no merge) the output rows
   int H, Hq, G, cap, tps, nsplit;
   float qscale;            // sm_scale log2(e) / sqrt(128) (the butterflies are unnormalized)
   uint16_t kcb16[16];      // fp16 levels of the key codebook (TurboQuant keys)
