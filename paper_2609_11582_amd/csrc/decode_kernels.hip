@@ -333,7 +333,6 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   __shared__ uint32_t wmask[kDecWaves];
   __shared__ uint32_t wnv[kDecWaves];  // value-norm maxima
   __shared__ int wexp[kDecWaves];      // operand scale exponents E
-  __shared__ __attribute__((aligned(16))) float fac[8][kDecWaves];    // per head and wave: combine factor
   __shared__ __attribute__((aligned(16))) _Float16 atile[8][kATile];  // merged rows, fp16
   static_assert(sizeof(float) * kD * kAccPitch <= kRingSlots * kSlotBytes, "a wave's combine rows fit in its ring");
   uint8_t* const ring = reinterpret_cast<uint8_t*>(ring_mem);
@@ -769,7 +768,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   }
 
   // ---- combine the waves of the work-group: every wave writes its raw accumulators and its
-  // per-head (m, l); the combining threads derive the factors 2^(m_w - M) themselves ----
+  // per-head (m, l); the combining waves derive the factors 2^(m_w - M) themselves ----
   l_run += fswap8(l_run);
   l_run = sum32(sum16(l_run));
   {
@@ -818,63 +817,80 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
   // 2^e / L with e = 15 - ilogb(n_max) keeps the fp16 A tile below 2^13.
   const float nmf = h2f(nmax);
   const int e = (nmf > 0.0f) ? 15 - min(max(ilogbf(nmf), -30), 20) : 0;
-  // factor table fac[head][wave] = 2^(m_w - M - E_w) 2^e / L (zero for heads >= G and empty waves):
-  // one thread per (head, wave)
-  if (tid < 8 * kDecWaves) {
-    const int hh = tid >> 3, w = tid & 7;
-    const float4 m0 = *reinterpret_cast<const float4*>(&wst[0][hh][0]);
-    const float4 m1 = *reinterpret_cast<const float4*>(&wst[0][hh][4]);
-    const float4 l0 = *reinterpret_cast<const float4*>(&wst[1][hh][0]);
-    const float4 l1 = *reinterpret_cast<const float4*>(&wst[1][hh][4]);
-    const float mv[8] = {m0.x, m0.y, m0.z, m0.w, m1.x, m1.y, m1.z, m1.w};
-    const float lv[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
-    float M = mv[0];
+  // Thread = (row quad rq, channel k): rows 4 rq .. 4 rq + 3 = heads 4 (rq & 1) .. + 3 of modality rq / 2
+  // (global rotation: two row quads, each the sum of rows 4 rq .. and 8 + 4 rq .., the two windows' parts).
+  // rq is uniform over a wave: waves 2 rq, 2 rq + 1 take quads 0-3 and, where text was seen, waves 0-3
+  // quads 4 and 5 (the same heads). The waves' rows are read before the factors are formed.
+  const int rq = wave >> 1, k = 64 * (wave & 1) + lane, h0 = 4 * (rq & 1);
+  const bool rows = !kGlobal || wave < 4;  // this wave sums rows
+  auto load_rows = [&](int quad, float4 (&v)[kDecWaves]) {
 #pragma unroll
-    for (int u = 1; u < kDecWaves; ++u) M = fmaxf(M, mv[u]);
-    float L = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kDecWaves; ++u) L += (mv[u] == -__builtin_inff()) ? 0.0f : lv[u] * fast_exp2(mv[u] - M);
-    const float sc = (hh < p.G && L > 0.0f) ? ldexpf(1.0f / L, e) : 0.0f;
-    // the wave's accumulators carry its operand scale 2^E_w
-    fac[hh][w] = (mv[w] == -__builtin_inff()) ? 0.0f : fast_exp2(mv[w] - M - (float)wexp[w]) * sc;
-    if (w == 0 && !kOne) {
+    for (int w = 0; w < kDecWaves; ++w) {
+      v[w] = *reinterpret_cast<const float4*>(&wacc(w)[k][4 * quad]);
+      if constexpr (kGlobal) {
+        const float4 v2 = *reinterpret_cast<const float4*>(&wacc(w)[k][8 + 4 * quad]);
+        v[w] = make_float4(v[w].x + v2.x, v[w].y + v2.y, v[w].z + v2.z, v[w].w + v2.w);
+      }
+    }
+  };
+  float4 v[kDecWaves];
+  if (rows) load_rows(rq, v);
+  // factor 2^(m_w - M - E_w) 2^e / L of head lane / 8 and wave lane % 8 (zero for heads >= G and empty waves),
+  // formed by every wave for itself: maximum and sum over the eight lanes of a head by DPP, then the 32
+  // factors of the wave's four heads as scalars (no table and barrier, and no branch per wave around the
+  // rows, whose reads are all in flight: 0.3-0.4 us of a decode call, 13.04 -> 12.75 us at 32768 tokens)
+  float fw[4][kDecWaves];
+  {
+    const int hh = lane >> 3, w = lane & 7;
+    const float mv = wst[0][hh][w], lv = wst[1][hh][w];
+    const int ew = wexp[w];
+    auto quad1 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false)); };
+    auto quad2 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x4E, 0xf, 0xf, false)); };
+    // the mirror of eight lanes: from any lane of one quad to one of the other, whose lanes agree by then
+    auto mirror8 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x141, 0xf, 0xf, false)); };
+    float M = fmaxf(mv, quad1(mv));
+    M = fmaxf(M, quad2(M));
+    M = fmaxf(M, mirror8(M));
+    const bool some = mv != -__builtin_inff();
+    float L = some ? lv * fast_exp2(mv - M) : 0.0f;
+    L += quad1(L);
+    L += quad2(L);
+    L += mirror8(L);
+    if (wave == 0 && w == 0 && !kOne) {
       rec[hh] = M;
       rec[8 + hh] = L;
     }
+    const float sc = (hh < p.G && L > 0.0f) ? ldexpf(1.0f / L, e) : 0.0f;
+    // the wave's accumulators carry its operand scale 2^E_w
+    const int f = __builtin_bit_cast(int, some ? fast_exp2(mv - M - (float)ew) * sc : 0.0f);
+    if (rows) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int u = 0; u < kDecWaves; ++u) fw[i][u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(f, 8 * (h0 + i) + u));
+    }
   }
-  __syncthreads();
-  // rows summed over the waves with their factors -> A tile [head][128 m + k] (fp16); thread =
-  // (row quad rq, channel k), rows 4 rq .. 4 rq + 3 = heads 4 (rq & 1) .. +3 of modality rq / 2
-  // (global rotation: two row quads, each the sum of rows 4 rq .. and 8 + 4 rq .., the two windows' parts)
-  for (int idx = tid; idx < (kGlobal ? 2 : 6) * kD; idx += 64 * kDecWaves) {
-    const int rq = idx >> 7, k = idx & (kD - 1), m = rq >> 1, h0 = 4 * (rq & 1);
-    if (!(mask & (1u << m))) continue;
+  // rows summed over the waves -> A tile [head][128 m + k] (fp16). Audio and video rows are there for every
+  // wave (zeros where it saw none); text rows only for the waves that saw text.
+  auto sum_rows = [&](int m, uint32_t waves) {
     float a[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int w4 = 0; w4 < kDecWaves; w4 += 4) {
-      float4 f[4];
+    for (int u = 0; u < kDecWaves; ++u) {
+      const float vu[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-      for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const float4*>(&fac[h0 + i][w4]);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (!(wmask[w4 + u] & (1u << m))) continue;  // that wave saw no token of this modality
-        float4 v = *reinterpret_cast<const float4*>(&wacc(w4 + u)[k][4 * rq]);
-        if constexpr (kGlobal) {
-          const float4 v2 = *reinterpret_cast<const float4*>(&wacc(w4 + u)[k][8 + 4 * rq]);
-          v = make_float4(v.x + v2.x, v.y + v2.y, v.z + v2.z, v.w + v2.w);
-        }
-        const float fu[4] = {u == 0 ? f[0].x : u == 1 ? f[0].y : u == 2 ? f[0].z : f[0].w,
-                             u == 0 ? f[1].x : u == 1 ? f[1].y : u == 2 ? f[1].z : f[1].w,
-                             u == 0 ? f[2].x : u == 1 ? f[2].y : u == 2 ? f[2].z : f[2].w,
-                             u == 0 ? f[3].x : u == 1 ? f[3].y : u == 2 ? f[3].z : f[3].w};
-        a[0] = __builtin_fmaf(v.x, fu[0], a[0]);
-        a[1] = __builtin_fmaf(v.y, fu[1], a[1]);
-        a[2] = __builtin_fmaf(v.z, fu[2], a[2]);
-        a[3] = __builtin_fmaf(v.w, fu[3], a[3]);
-      }
+      for (int i = 0; i < 4; ++i) a[i] = ((waves >> u) & 1u) ? __builtin_fmaf(vu[i], fw[i][u], a[i]) : a[i];
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) atile[h0 + i][m * kD + k] = (_Float16)a[i];
+  };
+  if (rows) sum_rows(kGlobal ? 0 : rq >> 1, 0xffu);
+  if (!kGlobal && (mask & 4u) && wave < 4) {
+    uint32_t waves = 0;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) waves |= ((wmask[w] >> 2) & 1u) << w;
+    waves = (uint32_t)__builtin_amdgcn_readfirstlane((int)waves);
+    load_rows(4 + rq, v);
+    sum_rows(2, waves);
   }
   __syncthreads();
   // ---- inverse rotation on MFMA, once per present modality: wave w < 4 computes channels
