@@ -936,8 +936,11 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
 // One work-group of 256 threads per (query head j, sequence b): thread (split group sg, channel
 // quad q4) sums the splits s = sg (mod 8). Every load is issued before any is used; empty splits
 // carry M = -inf and are skipped (their outputs are zeros). A record's L is relative to
-// 2^(M + kLazy) (the split kernel's lazily updated reference).
+// 2^(M + kLazy) (the split kernel's lazily updated reference). Latency bound (one round trip to memory, one
+// barrier): a wave's two split groups meet in registers, so that eight LDS rows became four and two barriers
+// one, 12.75 -> 12.41 us for a decode call at 32768 tokens, 19.2 -> 18.9 at 131072.
 constexpr int kMergeThreads = 256;
+constexpr int kMergeWaves = kMergeThreads / 64;
 constexpr int kMergeUnroll = 8;  // splits per thread held in registers at once
 
 // Eight split records of one chunk (splits s0, s0 + 8, ..., s0 + 56) for query head hd and channel
@@ -1010,53 +1013,57 @@ __device__ __forceinline__ void merge_splits(const float* base, int nsplit, int 
   }
 }
 
-// The 8 split groups combined: every group rescaled to the global max Mt; lanes of tid < 32 end
-// with the summed outputs of channels 4 tid .. 4 tid + 3 in `t` and the summed L in `Lt`.
-__device__ __forceinline__ void combine_groups(float M, float L, float4 o, int tid, float (&red)[2][kMergeThreads / 64],
-                                               float4 (&part)[8][32], float& Mt, float& Lt, float4& t) {
-  const int lane = tid & 63, wave = tid >> 6, q4 = tid & 31, sg = tid >> 5;
-  float mw = wave_max(M);
-  if (lane == 0) red[0][wave] = mw;
-  __syncthreads();
-  Mt = red[0][0];
+// The 8 split groups combined, one barrier. The wave's two groups (lanes 0-31, 32-63) meet in registers and
+// leave (max, sum) and the outputs in LDS; `final_parts` brings the waves into one frame.
+struct MergeShared {
+  float m[kMergeWaves], l[kMergeWaves];
+  float4 part[kMergeWaves][32];
+};
+
+__device__ __forceinline__ void stage_parts(float M, float L, float4 o, int lane, int wave, MergeShared& sh) {
+  const float mw = max32(M);
+  const float a = (M == -__builtin_inff()) ? 0.0f : exp2f(M - mw);
+  L = sum32(L * a);
+  o = make_float4(sum32(o.x * a), sum32(o.y * a), sum32(o.z * a), sum32(o.w * a));
+  if (lane < 32) sh.part[wave][lane] = o;
+  if (lane == 0) {
+    sh.m[wave] = mw;
+    sh.l[wave] = L;
+  }
+}
+
+// after the barrier: channel quad q4's outputs and the sum, both in the frame of the maximum Mt
+__device__ __forceinline__ void final_parts(const MergeShared& sh, int q4, float& Mt, float& Lt, float4& t) {
+  Mt = sh.m[0];
 #pragma unroll
-  for (int w = 1; w < kMergeThreads / 64; ++w) Mt = fmaxf(Mt, red[0][w]);
-  const float a = (M == -__builtin_inff()) ? 0.0f : exp2f(M - Mt);
-  // L is the same for every channel quad of a split group: count it once per group
-  float lw = (q4 == 0) ? L * a : 0.0f;
-  lw = wave_sum(lw);
-  if (lane == 0) red[1][wave] = lw;
-  part[sg][q4] = make_float4(o.x * a, o.y * a, o.z * a, o.w * a);
-  __syncthreads();
+  for (int w = 1; w < kMergeWaves; ++w) Mt = fmaxf(Mt, sh.m[w]);
   Lt = 0.0f;
   t = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (tid < 32) {
 #pragma unroll
-    for (int w = 0; w < kMergeThreads / 64; ++w) Lt += red[1][w];
-    t = part[0][tid];
-#pragma unroll
-    for (int g = 1; g < 8; ++g) {
-      const float4 u = part[g][tid];
-      t.x += u.x;
-      t.y += u.y;
-      t.z += u.z;
-      t.w += u.w;
-    }
+  for (int w = 0; w < kMergeWaves; ++w) {
+    const float f = (sh.m[w] == -__builtin_inff()) ? 0.0f : exp2f(sh.m[w] - Mt);
+    const float4 u = sh.part[w][q4];
+    Lt = __builtin_fmaf(f, sh.l[w], Lt);
+    t.x = __builtin_fmaf(f, u.x, t.x);
+    t.y = __builtin_fmaf(f, u.y, t.y);
+    t.z = __builtin_fmaf(f, u.z, t.z);
+    t.w = __builtin_fmaf(f, u.w, t.w);
   }
 }
 
 __global__ __launch_bounds__(kMergeThreads) void k_decode_merge(const float* __restrict__ ws, int H, int Hq, int G,
                                                                 int nsplit, float* __restrict__ out) {
-  __shared__ float red[2][kMergeThreads / 64];
-  __shared__ __attribute__((aligned(16))) float4 part[8][32];
+  __shared__ __attribute__((aligned(16))) MergeShared sh;
   const int j = blockIdx.x, b = blockIdx.y;
   const int h = j / G, hd = j % G;
   const int tid = threadIdx.x;
   float M, L, Mt, Lt;
   float4 o, t;
   merge_splits(ws + ((size_t)b * H + h) * nsplit * kRecFloats, nsplit, hd, tid >> 5, tid & 31, M, L, o);
-  combine_groups(M, L, o, tid, red, part, Mt, Lt, t);
+  stage_parts(M, L, o, tid & 63, tid >> 6, sh);
+  __syncthreads();
   if (tid < 32) {
+    final_parts(sh, tid, Mt, Lt, t);
     const float inv = (Lt > 0.0f) ? 1.0f / Lt : 0.0f;
     *reinterpret_cast<float4*>(out + ((size_t)b * Hq + j) * kD + 4 * tid) =
         make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv);
@@ -1084,237 +1091,282 @@ struct TailArgs {
   float qscale;            // sm_scale * log2(e): scores in base 2
 };
 
+// lane ^ 4 within each row of 16
+__device__ __forceinline__ float fswap4(float v) {
+  const int x = __builtin_bit_cast(int, v);
+  const int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0x5, false);  // banks 0, 2: lane + 4
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(t, x, 0x114, 0xf, 0xa, false));  // 1, 3: lane - 4
+}
+template <int kCtrl>
+__device__ __forceinline__ float fdpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
+}
+// value of the other half-row pair member: lane ^ 16, lane ^ 32
+__device__ __forceinline__ float fswap16(float v) {
+  uint32_t a, b;
+  swap16(__builtin_bit_cast(uint32_t, v), a, b);
+  return __builtin_bit_cast(float, (lane_id() & 16) ? a : b);
+}
+
+// A wave's 32 ring slots are scored, weighted and summed by that wave alone, in the frame of its own maximum, so
+// that the work-group meets twice: once for the query tables, once for the last sum. Scores run on mixed fp16 /
+// fp32 multiply-adds against tables that hold q' step 2^(24 - shift) (the codes enter as fp16 subnormals, as
+// in the split kernel) and the windows' q'.m once, not per token. Ring rows are taken by slot, whatever the length,
+// so that their loads do not wait for it. Bound by its chain (length, codes, tables, scores, outputs): 28 heads
+// over 64 splits took 6.8 us, 1.45 of it for the scores, 1.2 for the groups' two barriers; now 5.5.
+constexpr int kTabHalf = 68, kTabRow = 2 * kTabHalf;  // table pitches: a wave's broadcast reads hit distinct banks
+
 __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const float* __restrict__ ws, int H, int Hq,
                                                                          int G, int nsplit, float* __restrict__ out,
                                                                          TailArgs ta) {
-  __shared__ float red[2][kMergeThreads / 64];
-  __shared__ __attribute__((aligned(16))) float4 part[8][32];
-  __shared__ __attribute__((aligned(16))) float qp[kD];   // q sm_scale log2(e)
-  __shared__ __attribute__((aligned(16))) float qr[kD];   // H q sm_scale log2(e) (rotated query)
-  __shared__ float ps[kResidual];                         // tail scores, then weights
-  __shared__ __attribute__((aligned(16))) float ot[16][kD];  // tail output partials, 16 token groups
-  __shared__ float tred[kMergeThreads / 64];
-  __shared__ __attribute__((aligned(16))) float mst[4][2][kD];  // (minimum, step) of the tail's quantized windows
+  static_assert(kResidual == 32 * kMergeWaves, "a wave takes 32 ring slots");
+  __shared__ __attribute__((aligned(16))) MergeShared sh;
+  __shared__ __attribute__((aligned(16))) float qp[kTabRow];               // q sm_scale log2(e)
+  __shared__ __attribute__((aligned(16))) float qs[kMergeWaves][kTabRow];  // per quantized window: q' step, scaled
+  __shared__ float qbias[kMergeWaves];                                     // and q'.m
+  __shared__ float tm[kMergeWaves], tl[kMergeWaves];                       // tail: maximum and sum of a wave's slots
+  __shared__ __attribute__((aligned(16))) float ot[kMergeWaves][kD];       // and outputs
   const int j = blockIdx.x, b = blockIdx.y;
   const int h = j / G, hd = j % G;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sg = tid >> 5, q4 = tid & 31;
   const size_t seq = (size_t)b * H + h;
   const float* base = ws + seq * nsplit * kRecFloats;
 
-  // ---- every load goes out before any is used: the first chunk of split records, then (once the
-  // length is known) the query, the metadata of the tail's quantized windows, the tail's keys
-  // (codes and norms, or fp16 rows) and the value rows this thread sums ----
+  // ---- every load goes out before any is used: first what needs no length (split records, the query, the ring
+  // rows), then the tail's codes, norms and metadata ----
   const int len_dev = ta.seq_lens[b];  // first, a scalar load in flight while the records' loads go out
   SplitChunk ch0;
   if (sg < nsplit) load_split_chunk(base, nsplit, hd, q4, sg, ch0);
-  const int L = min(max(len_dev, 0), ta.cap);
-  const int T0 = max(L - kResidual, 0), nt = L - T0, Kq = L & ~(kResidual - 1);
-  // quantized keys [T0, Kq) lie in windows w0 .. w0 + 3 (Kq - T0 <= 128 and Kq is window aligned)
-  const int w0 = T0 / kW, nwq = (Kq > T0) ? (Kq - 1) / kW - w0 + 1 : 0;
-  // loaded by every thread (channel tid mod 128) and used after the barrier: a load inside a branch
-  // gets its use pulled in behind it, and the wait there holds back every later load
-  const uint32_t qx = ta.q[((size_t)b * Hq + j) * kD + (tid & (kD - 1))];
-  // and, for the rotation in wave 0, channels 4 l .. 4 l + 3 of lane l (mod 32) with their signs
-  const uint2 qrow4 = *reinterpret_cast<const uint2*>(ta.q + ((size_t)b * Hq + j) * kD + 4 * (lane & 31));
-  const uint32_t s4 = *reinterpret_cast<const uint32_t*>(ta.signs + 4 * (lane & 31));
-  // metadata entries idx = tid, tid + 256 of the (window, channel) table, as loaded (entries past the
-  // tail's windows read window w0's, never used): fp16 minimum and step, or the MXFP4 record's
-  // nibble bytes and block scales (channel 4q + i in nibble i of bytes 4q, 4q + 1 (minimum), 4q + 2,
-  // 4q + 3 (step); scales at 128 + 2 (c / 32), + 1)
-  uint32_t mraw[2], sraw[2], mnib[2], snib[2], scl[2];
-  {
-    // both formats' loads on every path (no branch: a branch between loads makes later ones wait
-    // behind earlier ones), from valid addresses: with MXFP4 records the fp16 loads read record bytes,
-    // and without them the record loads read the same window's fp16 minima (a record's bytes lie within
-    // its window's 256-byte row); the format picks which to decode
-    const bool mx = ta.k_mx != nullptr;
-    const uint16_t* kmin = mx ? reinterpret_cast<const uint16_t*>(ta.k_mx) : ta.k_min;
-    const uint16_t* kstep = mx ? reinterpret_cast<const uint16_t*>(ta.k_mx) : ta.k_step;
-    const uint8_t* kmx = mx ? ta.k_mx : reinterpret_cast<const uint8_t*>(ta.k_min);
-    const size_t mxstride = mx ? kMxRecord : 2 * kD;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int idx = tid + kMergeThreads * r;
-      const int ic = (idx < nwq * kD) ? idx : (idx & (kD - 1));
-      const int wi = ic >> 7, c = ic & (kD - 1);
-      const size_t w = seq * (ta.cap / kW) + w0 + wi;
-      mraw[r] = kmin[mx ? 0 : w * kD + c];
-      sraw[r] = kstep[mx ? 0 : w * kD + c];
-      const uint8_t* rec = kmx + w * mxstride;
-      const int qq = c >> 2, i = c & 3;
-      mnib[r] = rec[4 * qq + (i >> 1)];
-      snib[r] = rec[4 * qq + 2 + (i >> 1)];
-      scl[r] = *reinterpret_cast<const uint16_t*>(rec + 128 + 2 * (c >> 5));  // minimum's scale, step's scale
-    }
-  }
-  // scores: two threads per token tt = tid / 2, channels 64 half .. 64 half + 63
-  const int tt = tid >> 1, half = tid & 1, ti = T0 + tt;
-  const bool tok = tt < nt, quant = tok && ti < Kq;
-  // both forms of the token's key, loaded by every thread (clamped indices, branch-free): a load in
-  // a branch makes later loads wait behind it (the two branches share registers)
-  const int tc = min(ti, ta.cap - 1);
-  const uint4 kq = *reinterpret_cast<const uint4*>(ta.k_codes + (seq * ta.cap + tc) * 32 + 16 * half);
-  const uint32_t knrm = ta.k_norm[seq * ta.cap + tc];
+  // channels 4 q4 .. 4 q4 + 3 of the query and their signs (both halves of the wave)
+  const uint2 qrow4 = *reinterpret_cast<const uint2*>(ta.q + ((size_t)b * Hq + j) * kD + 4 * q4);
+  const uint32_t s4 = *reinterpret_cast<const uint32_t*>(ta.signs + 4 * q4);
+  // scores: two lanes per ring slot, channels 64 half .. 64 half + 63
+  const int slot = 32 * wave + (lane >> 1), half = lane & 1;
   uint4 kr[8];
-  {  // the token's ring row, or ring row 0 for a quantized key (one shared line, never used)
-    const int rr = quant ? 0 : (ti & (kResidual - 1));
-    const uint4* row = reinterpret_cast<const uint4*>(ta.k_res + (seq * kResidual + rr) * kD + 64 * half);
+  {
+    const uint4* row = reinterpret_cast<const uint4*>(ta.k_res + (seq * kResidual + slot) * kD + 64 * half);
 #pragma unroll
     for (int u = 0; u < 8; ++u) kr[u] = row[u];
   }
-  // output: thread (channel octet c8, token group tg) sums tokens tg, tg + 16, ..., tg + 112 (16-byte
-  // loads: a wave keeps fewer than 64 loads in flight, the most its counter tracks)
-  const int c8 = tid & 15, tg = tid >> 4;
-  uint4 vv[kResidual / 16];
+  // outputs: channel octet c8 of the eight slots whose weights lie in the lane's row of 16 (every ring row is
+  // finite; slots past the tail get weight 0)
+  const int c8 = lane & 15;
+  uint4 vv[8];
   {
-    const uint4* vr = reinterpret_cast<const uint4*>(ta.v_res + seq * kResidual * kD) + c8;
+    const uint4* vr = reinterpret_cast<const uint4*>(ta.v_res + (seq * kResidual + 32 * wave + 8 * (lane >> 4)) * kD);
 #pragma unroll
-    for (int u = 0; u < kResidual / 16; ++u)  // every ring row (finite); rows past the tail get weight 0
-      vv[u] = vr[((T0 + tg + 16 * u) & (kResidual - 1)) * (kD / 8)];
+    for (int u = 0; u < 8; ++u) vv[u] = vr[u * (kD / 8) + c8];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const int L = min(max(len_dev, 0), ta.cap);
+  const int T0 = max(L - kResidual, 0), Kq = L & ~(kResidual - 1);
+  // quantized keys [T0, Kq) lie in windows w0 .. w0 + 3 (Kq - T0 <= 128 and Kq is window aligned)
+  const int w0 = T0 / kW, nwq = (Kq > T0) ? (Kq - 1) / kW - w0 + 1 : 0;
+  const int ti = T0 + ((slot - T0) & (kResidual - 1));  // the slot's token
+  const bool tok = ti < L, quant = tok && ti < Kq;
+  const int tc = min(ti, ta.cap - 1);
+  const uint4 kq = *reinterpret_cast<const uint4*>(ta.k_codes + (seq * ta.cap + tc) * 32 + 16 * half);
+  const uint32_t knrm = ta.k_norm[seq * ta.cap + tc];
+  // metadata of window w0 + wave, channels 4 q4 .. + 3 (window w0's where the tail has fewer: never used). Both
+  // formats' loads on every path (a branch between loads makes later ones wait), from valid addresses: with MXFP4
+  // records the fp16 loads read record bytes, and without them the record loads read the window's fp16 minima (a
+  // record's bytes lie within its 256-byte row); the format picks which to decode
+  uint2 mraw, sraw;
+  uint32_t word, scl;
+  const bool mx = ta.k_mx != nullptr;
+  {
+    const uint16_t* kmin = mx ? reinterpret_cast<const uint16_t*>(ta.k_mx) : ta.k_min;
+    const uint16_t* kstep = mx ? reinterpret_cast<const uint16_t*>(ta.k_mx) : ta.k_step;
+    const uint8_t* kmx = mx ? ta.k_mx : reinterpret_cast<const uint8_t*>(ta.k_min);
+    const size_t w = seq * (ta.cap / kW) + w0 + (wave < nwq ? wave : 0);
+    mraw = *reinterpret_cast<const uint2*>(kmin + (mx ? 0 : w * kD + 4 * q4));
+    sraw = *reinterpret_cast<const uint2*>(kstep + (mx ? 0 : w * kD + 4 * q4));
+    const uint8_t* rec = kmx + w * (mx ? kMxRecord : 2 * kD);
+    word = *reinterpret_cast<const uint32_t*>(rec + 4 * q4);
+    scl = *reinterpret_cast<const uint16_t*>(rec + 128 + 2 * (q4 >> 3));  // minimum's scale, step's scale
   }
   __builtin_amdgcn_sched_barrier(0);  // every load above goes out before the first use
 
-  // ---- the query, plain and rotated (wave 0: the butterflies in registers), the metadata as fp32 ----
-  if (tid < kD) qp[tid] = h2f(qx) * ta.qscale;
-  if (wave == 0) {  // Sylvester order, h ascending: channel bits 0, 1 in the lane, bits 2..6 = lane bits 0..4
+  // ---- the splits (their records were loaded first) ----
+  {
+    float M = -__builtin_inff(), Ls = 0.0f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (sg < nsplit) fold_split_chunk(ch0, M, Ls, o);
+    for (int s0 = sg + 8 * kMergeUnroll; s0 < nsplit; s0 += 8 * kMergeUnroll) {
+      SplitChunk c;
+      load_split_chunk(base, nsplit, hd, q4, s0, c);
+      fold_split_chunk(c, M, Ls, o);
+    }
+    stage_parts(M, Ls, o, lane, wave, sh);
+  }
+
+  // ---- the query, plain and rotated (every wave: the butterflies in registers), and the wave's window table ----
+  {
     const uint32_t qw[2] = {qrow4.x, qrow4.y};
     float x[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float v = h2f((qw[i >> 1] >> (16 * (i & 1))) & 0xffffu);
-      x[i] = ((s4 >> (8 * i + 7)) & 1u) ? -v : v;
-    }
-    {
+    for (int i = 0; i < 4; ++i) x[i] = h2f((qw[i >> 1] >> (16 * (i & 1))) & 0xffffu);
+    if (tid < 32)
+      *reinterpret_cast<float4*>(&qp[kTabHalf * (q4 >> 4) + 4 * (q4 & 15)]) =
+          make_float4(x[0] * ta.qscale, x[1] * ta.qscale, x[2] * ta.qscale, x[3] * ta.qscale);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = ((s4 >> (8 * i + 7)) & 1u) ? -x[i] : x[i];
+    {  // Sylvester order, h ascending: channel bits 0, 1 in the lane, bits 2..6 = lane bits 0..4
       const float a = x[0] + x[1], c = x[0] - x[1], d = x[2] + x[3], e = x[2] - x[3];
       x[0] = a + d;
       x[2] = a - d;
       x[1] = c + e;
       x[3] = c - e;
     }
-#pragma unroll
-    for (int lb = 1; lb < 32; lb <<= 1) {
+    auto step = [&](int lb, auto&& partner) {
       const bool hi = (lane & lb) != 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float o = __shfl_xor(x[i], lb);
+        const float o = partner(x[i]);
         x[i] = hi ? o - x[i] : x[i] + o;
       }
-    }
+    };
+    step(1, [](float v) { return fdpp<0xB1>(v); });
+    step(2, [](float v) { return fdpp<0x4E>(v); });
+    step(4, [](float v) { return fswap4(v); });
+    step(8, [](float v) { return fswap8(v); });
+    step(16, [](float v) { return fswap16(v); });
     const float sc = ta.qscale * 0.08838834764831845f;  // 1 / sqrt(128): H is orthonormal
-    if (lane < 32) *reinterpret_cast<float4*>(&qr[4 * lane]) = make_float4(x[0] * sc, x[1] * sc, x[2] * sc, x[3] * sc);
-  }
+    float mn[4], st[4], bias = 0.0f;
 #pragma unroll
-  for (int r = 0; r < 2; ++r) {
-    const int idx = tid + kMergeThreads * r;
-    if (idx < nwq * kD) {
-      float mn, st;
-      if (ta.k_mx) {
-        const int i = idx & 3;
-        mn = e2m1_decode((mnib[r] >> (4 * (i & 1))) & 15u, (int)(scl[r] & 0xffu) - 127);
-        st = e2m1_decode((snib[r] >> (4 * (i & 1))) & 15u, (int)(scl[r] >> 8) - 127);
+    for (int i = 0; i < 4; ++i) {
+      const float xr = x[i] * sc;
+      if (mx) {  // channel 4 q4 + i in nibble i of the word's halves (minima, steps)
+        mn[i] = e2m1_decode((word >> (4 * i)) & 15u, (int)(scl & 0xffu) - 127);
+        st[i] = e2m1_decode((word >> (16 + 4 * i)) & 15u, (int)(scl >> 8) - 127);
       } else {
-        mn = h2f(mraw[r]);
-        st = h2f(sraw[r]);
+        mn[i] = h2f(((i < 2 ? mraw.x : mraw.y) >> (16 * (i & 1))) & 0xffffu);
+        st[i] = h2f(((i < 2 ? sraw.x : sraw.y) >> (16 * (i & 1))) & 0xffffu);
       }
-      mst[idx >> 7][0][idx & (kD - 1)] = mn;
-      mst[idx >> 7][1][idx & (kD - 1)] = st;
+      bias = __builtin_fmaf(xr, mn[i], bias);
+      // channel pair j = 2 (q4 & 3) + i / 2 of its 16-channel code word
+      const int pair = 2 * (q4 & 3) + (i >> 1);
+      st[i] = xr * st[i] * __builtin_bit_cast(float, (uint32_t)(127 + 24 - (pair <= 4 ? 2 * pair : 2 * pair - 10)) << 23);
     }
+    bias += fdpp<0xB1>(bias);
+    bias += fdpp<0x4E>(bias);
+    bias += fswap4(bias);
+    bias += fswap8(bias);
+    bias = sum16(bias);
+    if (lane < 32 && wave < nwq)
+      *reinterpret_cast<float4*>(&qs[wave][kTabHalf * (q4 >> 4) + 4 * (q4 & 15)]) =
+          make_float4(st[0], st[1], st[2], st[3]);
+    if (lane == 0) qbias[wave] = bias;
   }
   __syncthreads();
 
-  // ---- tail scores ----
-  {
-    float sc = -__builtin_inff();
-    if (tok) {
-      float acc = 0.0f;
-      if (quant) {  // n16 (q' . (m + step code)) over the window's metadata
-        const uint32_t words[4] = {kq.x, kq.y, kq.z, kq.w};
-        const float* mrow = mst[ti / kW - w0][0];
-        const float* srow = mst[ti / kW - w0][1];
+  // ---- tail scores of the wave's slots (base 2) ----
+  float sc = 0.0f;
+  if (quant) {  // n16 (q'.m + (q' step).code) over the window's table
+    const uint32_t words[4] = {kq.x, kq.y, kq.z, kq.w};
+    const float* row = &qs[ti / kW - w0][kTabHalf * half];
+    float acc[2] = {0.0f, 0.0f};
 #pragma unroll
-        for (int cc = 0; cc < 64; ++cc) {
-          const int c = 64 * half + cc;
-          const uint32_t code = (words[cc >> 4] >> (16 * (c & 1) + (c & 14))) & 3u;
-          acc = __builtin_fmaf(qr[c], __builtin_fmaf(srow[c], (float)code, mrow[c]), acc);
-        }
-        acc *= h2f(knrm);
-      } else {  // fp16 key from the ring
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t d = words[u], ds = d >> 10;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const uint32_t xs[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int c = 64 * half + 8 * u + 2 * e;
-            acc = __builtin_fmaf(qp[c], h2f(xs[e] & 0xffffu), acc);
-            acc = __builtin_fmaf(qp[c + 1], h2f(xs[e] >> 16), acc);
-          }
-        }
+      for (int e = 0; e < 8; e += 2) {
+        const float4 t = *reinterpret_cast<const float4*>(&row[16 * u + 2 * e]);
+        const uint32_t c0 = e < 5 ? d & (0x00030003u << (2 * e)) : ds & (0x00030003u << (2 * e - 10));
+        const uint32_t c1 = e + 1 < 5 ? d & (0x00030003u << (2 * e + 2)) : ds & (0x00030003u << (2 * e - 8));
+        acc[0] = __builtin_fmaf(lo_f16(c0), t.x, acc[0]);
+        acc[1] = __builtin_fmaf(hi_f16(c0), t.y, acc[1]);
+        acc[0] = __builtin_fmaf(lo_f16(c1), t.z, acc[0]);
+        acc[1] = __builtin_fmaf(hi_f16(c1), t.w, acc[1]);
       }
-      acc += __shfl_xor(acc, 1);  // the token's two threads are both active or both not
-      sc = acc;
     }
-    if (half == 0) ps[tt] = sc;
-    float mw = wave_max(sc);
-    if (lane == 0) tred[wave] = mw;
-  }
-  __syncthreads();
-  float mtail = tred[0];
+    sc = acc[0] + acc[1];
+    if (half == 0) sc += qbias[ti / kW - w0];
+    sc *= h2f(knrm);
+  } else if (tok) {  // fp16 key from the ring
+    const float* row = &qp[kTabHalf * half];
+    float acc[2] = {0.0f, 0.0f};
 #pragma unroll
-  for (int w = 1; w < kMergeThreads / 64; ++w) mtail = fmaxf(mtail, tred[w]);
-  // weights 2^(s - mtail) (mtail = -inf only for an empty tail, which has no tokens)
-  if (tid < nt) ps[tid] = exp2f(ps[tid] - mtail);
-  __syncthreads();
+    for (int u = 0; u < 8; ++u) {
+      const uint32_t xs[4] = {kr[u].x, kr[u].y, kr[u].z, kr[u].w};
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        const float4 t = *reinterpret_cast<const float4*>(&row[8 * u + 2 * e]);
+        acc[0] = __builtin_fmaf(lo_f16(xs[e]), t.x, acc[0]);
+        acc[1] = __builtin_fmaf(hi_f16(xs[e]), t.y, acc[1]);
+        acc[0] = __builtin_fmaf(lo_f16(xs[e + 1]), t.z, acc[0]);
+        acc[1] = __builtin_fmaf(hi_f16(xs[e + 1]), t.w, acc[1]);
+      }
+    }
+    sc = acc[0] + acc[1];
+  }
+  sc += fdpp<0xB1>(sc);  // the slot's two lanes
+  float mt = tok ? sc : -__builtin_inff();
+  mt = fmaxf(mt, fdpp<0x4E>(mt));
+  mt = fmaxf(mt, fswap4(mt));
+  mt = fmaxf(mt, fswap8(mt));
+  mt = max32(max16(mt));
+  // weights 2^(s - mt) (mt = -inf only where the wave has no token)
+  const float pw = tok ? exp2f(sc - mt) : 0.0f;
+  float lt = pw;
+  lt += fdpp<0x4E>(lt);
+  lt += fswap4(lt);
+  lt += fswap8(lt);
+  lt = sum32(sum16(lt));
   {
     float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // slot 8 (lane / 16) + u of the wave: its weight is in lane 2 u of the lane's row of 16
+    const float ps[8] = {fdpp<0x150>(pw), fdpp<0x152>(pw), fdpp<0x154>(pw), fdpp<0x156>(pw),
+                         fdpp<0x158>(pw), fdpp<0x15A>(pw), fdpp<0x15C>(pw), fdpp<0x15E>(pw)};
 #pragma unroll
-    for (int u = 0; u < kResidual / 16; ++u) {
-      const int t2 = tg + 16 * u;
-      const float p = (t2 < nt) ? ps[t2] : 0.0f;
+    for (int u = 0; u < 8; ++u) {
       const uint32_t w4[4] = {vv[u].x, vv[u].y, vv[u].z, vv[u].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        o[2 * e] = __builtin_fmaf(p, h2f(w4[e] & 0xffffu), o[2 * e]);
-        o[2 * e + 1] = __builtin_fmaf(p, h2f(w4[e] >> 16), o[2 * e + 1]);
+        o[2 * e] = __builtin_fmaf(lo_f16(w4[e]), ps[u], o[2 * e]);
+        o[2 * e + 1] = __builtin_fmaf(hi_f16(w4[e]), ps[u], o[2 * e + 1]);
       }
     }
-    *reinterpret_cast<float4*>(&ot[tg][8 * c8]) = make_float4(o[0], o[1], o[2], o[3]);
-    *reinterpret_cast<float4*>(&ot[tg][8 * c8 + 4]) = make_float4(o[4], o[5], o[6], o[7]);
-  }
-  if (wave == 0) {  // sum of the weights
-    float lsum = 0.0f;
-    for (int t2 = lane; t2 < nt; t2 += 64) lsum += ps[t2];
-    lsum = wave_sum(lsum);
-    if (lane == 0) tred[0] = lsum;
-  }
-
-  // ---- the splits, then everything in the frame of the true maximum ----
-  float M = -__builtin_inff(), Ls = 0.0f, Mt, Lt;
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f), t;
-  if (sg < nsplit) fold_split_chunk(ch0, M, Ls, o);
-  for (int s0 = sg + 8 * kMergeUnroll; s0 < nsplit; s0 += 8 * kMergeUnroll) {
-    SplitChunk c;
-    load_split_chunk(base, nsplit, hd, q4, s0, c);
-    fold_split_chunk(c, M, Ls, o);
-  }
-  combine_groups(M, Ls, o, tid, red, part, Mt, Lt, t);  // (its barriers also order the tail's LDS writes)
-  const float ltail = tred[0];
-  if (tid < 32) {
-    const float mref = Mt + kLazy;  // the splits' sums are relative to 2^(Mt + kLazy)
-    const float mf = fmaxf(mref, mtail);
-    const float as = (Mt == -__builtin_inff()) ? 0.0f : exp2f(mref - mf);
-    const float at = (nt == 0) ? 0.0f : exp2f(mtail - mf);
-    const float ltot = Lt * as + ltail * at;
-    const float inv = (ltot > 0.0f) ? 1.0f / ltot : 0.0f;
-    float4 tv = *reinterpret_cast<const float4*>(&ot[0][4 * tid]);
 #pragma unroll
-    for (int g2 = 1; g2 < 16; ++g2) {
-      const float4 u = *reinterpret_cast<const float4*>(&ot[g2][4 * tid]);
-      tv = make_float4(tv.x + u.x, tv.y + u.y, tv.z + u.z, tv.w + u.w);
+    for (int e = 0; e < 8; ++e) o[e] = sum32(sum16(o[e]));
+    if (lane < 16) {
+      *reinterpret_cast<float4*>(&ot[wave][8 * c8]) = make_float4(o[0], o[1], o[2], o[3]);
+      *reinterpret_cast<float4*>(&ot[wave][8 * c8 + 4]) = make_float4(o[4], o[5], o[6], o[7]);
     }
-    const float r[4] = {(t.x * as + tv.x * at) * inv, (t.y * as + tv.y * at) * inv, (t.z * as + tv.z * at) * inv,
-                        (t.w * as + tv.w * at) * inv};
-    *reinterpret_cast<float4*>(out + ((size_t)b * Hq + j) * kD + 4 * tid) = make_float4(r[0], r[1], r[2], r[3]);
+    if (lane == 0) {
+      tm[wave] = mt;
+      tl[wave] = lt;
+    }
+  }
+  __syncthreads();
+
+  // ---- the splits' and the waves' parts in the frame of the true maximum ----
+  if (tid < 32) {
+    float Mt, Lt;
+    float4 t;
+    final_parts(sh, q4, Mt, Lt, t);
+    const float mref = Mt + kLazy;  // the splits' sums are relative to 2^(Mt + kLazy)
+    float mf = mref;
+#pragma unroll
+    for (int w = 0; w < kMergeWaves; ++w) mf = fmaxf(mf, tm[w]);
+    const float as = (Mt == -__builtin_inff()) ? 0.0f : exp2f(mref - mf);
+    float ltot = Lt * as;
+    t = make_float4(t.x * as, t.y * as, t.z * as, t.w * as);
+#pragma unroll
+    for (int w = 0; w < kMergeWaves; ++w) {
+      const float f = (tm[w] == -__builtin_inff()) ? 0.0f : exp2f(tm[w] - mf);
+      const float4 u = *reinterpret_cast<const float4*>(&ot[w][4 * q4]);
+      ltot = __builtin_fmaf(f, tl[w], ltot);
+      t.x = __builtin_fmaf(f, u.x, t.x);
+      t.y = __builtin_fmaf(f, u.y, t.y);
+      t.z = __builtin_fmaf(f, u.z, t.z);
+      t.w = __builtin_fmaf(f, u.w, t.w);
+    }
+    const float inv = (ltot > 0.0f) ? 1.0f / ltot : 0.0f;
+    *reinterpret_cast<float4*>(out + ((size_t)b * Hq + j) * kD + 4 * q4) =
+        make_float4(t.x * inv, t.y * inv, t.z * inv, t.w * inv);
   }
 }
 
