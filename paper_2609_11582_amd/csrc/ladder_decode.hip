@@ -94,6 +94,12 @@ struct LTile {
   uint2 meta;            // 8 bytes of the window's (minimum, step) rows (method keys)
 };
 
+// a value of another of the lane's eight: quad xor 1 (0xB1), xor 2 (0x4E), the half row mirrored (0x141)
+template <int kCtrl>
+__device__ __forceinline__ float dpp8(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
+}
+
 // kOne: one split per sequence, which writes the output rows instead of a record
 template <int kKB, int kVB, bool kTq, bool kOne>
 __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) {
@@ -114,7 +120,6 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
   __shared__ float wst[2][8][kLw];
   __shared__ uint32_t wmask[kLw], nv_all;  // nv_all: the largest value norm (fp32 bits, non-negative)
   __shared__ int wexp[kLw];
-  __shared__ __attribute__((aligned(16))) float fac[kLw][8];      // combine factor per wave and head
   __shared__ __attribute__((aligned(16))) float ttx[kLw][kD][8];  // text rows (heads 0-7) per wave, swizzled
   __shared__ float amax_w[4];
 
@@ -583,45 +588,59 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
   // merged rows divided by L are convex combinations of n_v cb vectors (|cb| < 1/4): the factor
   // 2^e / L with e = 13 - ilogb(n_max) keeps the fp16 A tile below 2^12
   const int e = (nmax > 0.0f) ? 13 - min(max(ilogbf(nmax), -30), 20) : 0;
-  if (tid < 8 * kLw) {
-    const int hh = tid >> 3, w = tid & 7;
-    float M = -__builtin_inff();
+  // A tile [head][128 m + k] (fp16): the waves' rows summed with their factors, in wave order; thread = (row
+  // quad rq, channel k), rows 4 rq .. 4 rq + 3 = heads 4 (rq & 1) .. + 3 of modality rq / 2. rq is uniform over a
+  // wave: waves 2 rq, 2 rq + 1 take quads 0-3 and, where text was seen, waves 0-3 quads 4 and 5 (the same heads).
+  // The rows are read before the factors are formed.
+  const int rq = wave >> 1, k = 64 * (wave & 1) + lane, h0 = 4 * (rq & 1);
+  float4 v[kLw];
 #pragma unroll
-    for (int u = 0; u < kLw; ++u) M = fmaxf(M, wst[0][hh][u]);
-    float L = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kLw; ++u)
-      L += (wst[0][hh][u] == -__builtin_inff()) ? 0.0f : wst[1][hh][u] * __builtin_amdgcn_exp2f(wst[0][hh][u] - M);
-    const float scl = (hh < p.G && L > 0.0f) ? ldexpf(1.0f / L, e) : 0.0f;
-    // the wave's accumulators carry its operand scale 2^E_w
-    fac[w][hh] = (wst[0][hh][w] == -__builtin_inff())
-                     ? 0.0f
-                     : __builtin_amdgcn_exp2f(wst[0][hh][w] - M - (float)wexp[w]) * scl;
-    if (w == 0 && !kOne) {
+  for (int w = 0; w < kLw; ++w) v[w] = *reinterpret_cast<const float4*>(wacc + row_ofs(w, k, rq));
+  // factor 2^(m_w - M - E_w) 2^e / L of head lane / 8 and wave lane % 8 (zero for heads >= G and empty waves), formed
+  // by every wave for itself: maximum and sum over the eight lanes of a head by DPP, then the 32 factors of the
+  // wave's four heads as scalars (a table of them cost a barrier and an LDS read per row:
+  // 4-bit codes at 32768 tokens 17.2 -> 16.5 us)
+  float fw[4][kLw];
+  {
+    const int hh = lane >> 3, w = lane & 7;
+    const float mv = wst[0][hh][w], lv = wst[1][hh][w];
+    const int ew = wexp[w];
+    float M = fmaxf(mv, dpp8<0xB1>(mv));
+    M = fmaxf(M, dpp8<0x4E>(M));
+    M = fmaxf(M, dpp8<0x141>(M));
+    const bool some = mv != -__builtin_inff();
+    float L = some ? lv * __builtin_amdgcn_exp2f(mv - M) : 0.0f;
+    L += dpp8<0xB1>(L);
+    L += dpp8<0x4E>(L);
+    L += dpp8<0x141>(L);
+    if (wave == 0 && w == 0 && !kOne) {
       rec[hh] = M;
       rec[8 + hh] = L;
     }
-  }
-  __syncthreads();
-  // A tile [head][128 m + k] (fp16): the waves' rows summed with their factors, in wave order;
-  // thread = (row quad rq, channel k), rows 4 rq .. 4 rq + 3 = heads 4 (rq & 1) .. + 3 of modality rq / 2
-  for (int idx = tid; idx < 6 * kD; idx += 64 * kLw) {
-    const int rq = idx >> 7, k = idx & (kD - 1), m = rq >> 1, hq = rq & 1;
-    float a[4] = {0.f, 0.f, 0.f, 0.f};
-    if (mask & (1u << m)) {
+    const float scl = (hh < p.G && L > 0.0f) ? ldexpf(1.0f / L, e) : 0.0f;
+    // the wave's accumulators carry its operand scale 2^E_w
+    const int f = __builtin_bit_cast(int, some ? __builtin_amdgcn_exp2f(mv - M - (float)ew) * scl : 0.0f);
 #pragma unroll
-      for (int w = 0; w < kLw; ++w) {
-        const float4 f = *reinterpret_cast<const float4*>(&fac[w][4 * hq]);
-        const float4 v = (m < 2) ? *reinterpret_cast<const float4*>(wacc + row_ofs(w, k, rq))
-                                 : *reinterpret_cast<const float4*>(&ttx[w][0][0] + text_ofs(k, hq));
-        a[0] = __builtin_fmaf(f.x, v.x, a[0]);
-        a[1] = __builtin_fmaf(f.y, v.y, a[1]);
-        a[2] = __builtin_fmaf(f.z, v.z, a[2]);
-        a[3] = __builtin_fmaf(f.w, v.w, a[3]);
-      }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < kLw; ++u) fw[i][u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(f, 8 * (h0 + i) + u));
+  }
+  auto sum_rows = [&](int m) {
+    float a[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < kLw; ++u) {
+      const float vu[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = __builtin_fmaf(vu[i], fw[i][u], a[i]);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) atile[4 * hq + i][m * kD + k] = (_Float16)a[i];
+    for (int i = 0; i < 4; ++i) atile[h0 + i][m * kD + k] = (_Float16)a[i];
+  };
+  sum_rows(rq >> 1);
+  if ((mask & 4u) && wave < 4) {
+#pragma unroll
+    for (int w = 0; w < kLw; ++w) v[w] = *reinterpret_cast<const float4*>(&ttx[w][0][0] + text_ofs(k, rq));
+    sum_rows(2);
   }
   __syncthreads();
   floatx4 dacc = {0.f, 0.f, 0.f, 0.f};
