@@ -340,6 +340,13 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
 
   auto compute = [&](int it, const LTile<kKB, kVB>& lt) {
     const int t0 = t_begin + (wave + kLw * it) * kW;
+    // the younger of a SIMD's two waves leads in every second round counted from the last (else the older one
+    // wins every issue and leaves it behind): 131072 tokens at 3 bits 33.7 -> 32.6 us, 4 x 65536 at 4 bits 54.4 ->
+    // 53.7. Not in the last two rounds: splits of two were 2 % slower with it (32768 tokens at 3 bits 17.0 -> 17.25)
+    if (wave >= kLw / 2 && !((nmine - it) & 1) && nmine - it > 2)
+      __builtin_amdgcn_s_setprio(1);
+    else
+      __builtin_amdgcn_s_setprio(0);
     // ---- key operands ----
     float bias = 0.0f;   // q' . m of this window for head r (method keys), fp32
     uint32_t bq[4][4];   // B operands: fp16(q'_c step_c 2^k0) (method keys), or the query itself
@@ -548,6 +555,7 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
     compute(it, ta);
   }
 
+  __builtin_amdgcn_s_setprio(0);
   // ---- epilogue: the inverse-rotation slice of this wave (output channels 16 wave .. + 15) ----
   uint4 rb[12];
   {
