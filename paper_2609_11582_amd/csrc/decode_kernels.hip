@@ -38,6 +38,7 @@
 #include <cstdlib>
 
 #include "launch.hpp"
+#include "wave_ops.hpp"
 
 namespace okvq {
 
@@ -92,55 +93,11 @@ __device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
 }
 // 2^x on the hardware unit; results below 2^-126 flush to zero (weights that small do not count)
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// lane l <- lane l ^ 8 within each row of 16 lanes (DPP row rotate by 8)
-constexpr int kRowRor8 = 0x128;
-__device__ __forceinline__ float fswap8(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kRowRor8, 0xf, 0xf, false));
-}
 // lanes of the given banks (4-lane groups of each row; 0x3 = lanes 0-7, 0xc = lanes 8-15) take
 // lane ^ 8's src, the others keep old
 template <int kBanks>
 __device__ __forceinline__ uint32_t take_partner(uint32_t old, uint32_t src) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)src, kRowRor8, 0xf, kBanks, false);
-}
-// Pairwise combination of lanes l and l ^ 16 (or l ^ 32) with the VALU row swaps of gfx950
-// (v_permlane16_swap / v_permlane32_swap): swapping a register with a copy of itself leaves the
-// lane's own value in one result and its partner's in the other, so a symmetric op of the two
-// results is the pair's value in both lanes, with no LDS-pipe shuffle. The copy is made opaque:
-// given the same value twice, the compiler folds the two results into one.
-__device__ __forceinline__ uint32_t opaque_copy(uint32_t v) {
-  __asm__ volatile("" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ void swap16(uint32_t v, uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(v, opaque_copy(v), false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ __forceinline__ void swap32(uint32_t v, uint32_t& a, uint32_t& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(v, opaque_copy(v), false, false);
-  a = r[0];
-  b = r[1];
-}
-__device__ __forceinline__ float sum16(float v) {
-  uint32_t a, b;
-  swap16(__builtin_bit_cast(uint32_t, v), a, b);
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-__device__ __forceinline__ float sum32(float v) {
-  uint32_t a, b;
-  swap32(__builtin_bit_cast(uint32_t, v), a, b);
-  return __builtin_bit_cast(float, a) + __builtin_bit_cast(float, b);
-}
-__device__ __forceinline__ float max16(float v) {
-  uint32_t a, b;
-  swap16(__builtin_bit_cast(uint32_t, v), a, b);
-  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
-}
-__device__ __forceinline__ float max32(float v) {
-  uint32_t a, b;
-  swap32(__builtin_bit_cast(uint32_t, v), a, b);
-  return fmaxf(__builtin_bit_cast(float, a), __builtin_bit_cast(float, b));
 }
 __device__ __forceinline__ uint32_t pkmax16(uint32_t v);
 __device__ __forceinline__ uint32_t pkmax32(uint32_t v);
@@ -160,17 +117,6 @@ __device__ __forceinline__ uint32_t pkmax32(uint32_t v) {
   swap32(v, a, b);
   return pkmax_u16(a, b);
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int lb = 1; lb < 64; lb <<= 1) v = fmaxf(v, __shfl_xor(v, lb));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int lb = 1; lb < 64; lb <<= 1) v += __shfl_xor(v, lb);
-  return v;
-}
-
 // fp16 bit pattern of 2^nvb (nvb in 0..16; 2^16 maps to +inf, which no stored norm reaches).
 __device__ __forceinline__ uint32_t norm_threshold(int nvb) { return (uint32_t)(nvb + 15) << 10; }
 // Smallest nvb in [nvb0, 16] with every lane's norms (two fp16 halves of `nv`, non-negative and
@@ -415,30 +361,14 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
       const float v = h2f((rr[i >> 1] >> (16 * (i & 1))) & 0xffffu);
       x[i] = ((qsgn >> (8 * i + 7)) & 1u) ? -v : v;
     }
-    {  // channel bits 0, 1 in lane
-      const float a = x[0] + x[1], c = x[0] - x[1], d = x[2] + x[3], e = x[2] - x[3];
-      x[0] = a + d;
-      x[2] = a - d;
-      x[1] = c + e;
-      x[3] = c - e;
-    }
-#pragma unroll
-    for (int lb = 1; lb < 32; lb <<= 1) {  // channel bits 2..6 are lane bits 0..4
-      const bool hi = (lane & lb) != 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float o = __shfl_xor(x[i], lb);
-        x[i] = hi ? o - x[i] : x[i] + o;
-      }
-    }
+    hadamard_row(x, lane);
     float am = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       x[i] *= p.qscale;
       am = fmaxf(am, fabsf(x[i]));
     }
-#pragma unroll
-    for (int lb = 1; lb < 64; lb <<= 1) am = fmaxf(am, __shfl_xor(am, lb));
+    am = wave_max(am);
     if (lane == 0) amax_w[wave] = am;
     *reinterpret_cast<float4*>(&qs[hr][c4]) = make_float4(x[0], x[1], x[2], x[3]);  // zero rows for heads >= G
   }
@@ -1102,23 +1032,6 @@ struct TailArgs {
   float qscale;            // sm_scale * log2(e): scores in base 2
 };
 
-// lane ^ 4 within each row of 16
-__device__ __forceinline__ float fswap4(float v) {
-  const int x = __builtin_bit_cast(int, v);
-  const int t = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0x5, false);  // banks 0, 2: lane + 4
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(t, x, 0x114, 0xf, 0xa, false));  // 1, 3: lane - 4
-}
-template <int kCtrl>
-__device__ __forceinline__ float fdpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
-}
-// value of the other half-row pair member: lane ^ 16, lane ^ 32
-__device__ __forceinline__ float fswap16(float v) {
-  uint32_t a, b;
-  swap16(__builtin_bit_cast(uint32_t, v), a, b);
-  return __builtin_bit_cast(float, (lane_id() & 16) ? a : b);
-}
-
 // A wave's 32 ring slots are scored, weighted and summed by that wave alone, in the frame of its own maximum, so
 // that the work-group meets twice: once for the query tables, once for the last sum. Scores run on mixed fp16 /
 // fp32 multiply-adds against tables that hold q' step 2^(24 - shift) (the codes enter as fp16 subnormals, as
@@ -1224,26 +1137,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const f
           make_float4(x[0] * ta.qscale, x[1] * ta.qscale, x[2] * ta.qscale, x[3] * ta.qscale);
 #pragma unroll
     for (int i = 0; i < 4; ++i) x[i] = ((s4 >> (8 * i + 7)) & 1u) ? -x[i] : x[i];
-    {  // Sylvester order, h ascending: channel bits 0, 1 in the lane, bits 2..6 = lane bits 0..4
-      const float a = x[0] + x[1], c = x[0] - x[1], d = x[2] + x[3], e = x[2] - x[3];
-      x[0] = a + d;
-      x[2] = a - d;
-      x[1] = c + e;
-      x[3] = c - e;
-    }
-    auto step = [&](int lb, auto&& partner) {
-      const bool hi = (lane & lb) != 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float o = partner(x[i]);
-        x[i] = hi ? o - x[i] : x[i] + o;
-      }
-    };
-    step(1, [](float v) { return fdpp<0xB1>(v); });
-    step(2, [](float v) { return fdpp<0x4E>(v); });
-    step(4, [](float v) { return fswap4(v); });
-    step(8, [](float v) { return fswap8(v); });
-    step(16, [](float v) { return fswap16(v); });
+    hadamard_row(x, lane);  // Sylvester order, h ascending
     const float sc = ta.qscale * 0.08838834764831845f;  // 1 / sqrt(128): H is orthonormal
     float mn[4], st[4], bias = 0.0f;
 #pragma unroll
