@@ -31,6 +31,7 @@
 #include <cstdlib>
 
 #include "launch.hpp"
+#include "wave_ops.hpp"
 
 namespace okvq {
 namespace {
@@ -93,12 +94,6 @@ struct LTile {
   uint32_t md[2];        // their modality bytes
   uint2 meta;            // 8 bytes of the window's (minimum, step) rows (method keys)
 };
-
-// a value of another of the lane's eight: quad xor 1 (0xB1), xor 2 (0x4E), the half row mirrored (0x141)
-template <int kCtrl>
-__device__ __forceinline__ float dpp8(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl, 0xf, 0xf, false));
-}
 
 // kOne: one split per sequence, which writes the output rows instead of a record
 template <int kKB, int kVB, bool kTq, bool kOne>
@@ -252,30 +247,14 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
 #pragma unroll
       for (int i = 0; i < 4; ++i) x[i] = ((sg >> (8 * i + 7)) & 1u) ? -v[i] : v[i];
     }
-    {  // channel bits 0, 1 inside the lane
-      const float a = x[0] + x[1], c = x[0] - x[1], d = x[2] + x[3], e = x[2] - x[3];
-      x[0] = a + d;
-      x[2] = a - d;
-      x[1] = c + e;
-      x[3] = c - e;
-    }
-#pragma unroll
-    for (int lb = 1; lb < 32; lb <<= 1) {  // channel bits 2 .. 6 are lane bits 0 .. 4
-      const bool hi = (lane & lb) != 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float o = __shfl_xor(x[i], lb);
-        x[i] = hi ? o - x[i] : x[i] + o;
-      }
-    }
+    hadamard_row(x, lane);
     float am = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       x[i] *= p.qscale;
       am = fmaxf(am, fabsf(x[i]));
     }
-#pragma unroll
-    for (int lb = 1; lb < 64; lb <<= 1) am = fmaxf(am, __shfl_xor(am, lb));
+    am = wave_max(am);
     if (lane == 0) amax_w[wave] = am;
     if (tid == 0) nv_all = 0u;
     *reinterpret_cast<float4*>(&qs[hr][c4]) = make_float4(x[0], x[1], x[2], x[3]);
@@ -430,8 +409,7 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
     // mx is the lane's maximum; a head's maximum over its four lane groups is needed only where the
     // reference moves (a lane above m_run + kLazyL puts its head above it too)
     auto head_max = [](float v) {
-      v = fmaxf(v, __shfl_xor(v, 16));
-      return fmaxf(v, __shfl_xor(v, 32));
+      return max32(max16(v));
     };
     float nvl = 0.0f;  // the lane's largest value norm so far, this window's included
 #pragma unroll
@@ -563,8 +541,7 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
 #pragma unroll
     for (int kk = 0; kk < 12; ++kk) rb[kk] = rp[4 * kk];
   }
-  float l_tot = l_part + __shfl_xor(l_part, 16);
-  l_tot += __shfl_xor(l_tot, 32);
+  const float l_tot = sum32(sum16(l_part));
   // the largest value norm: a maximum over each 16-lane row by DPP rotations, then one LDS atomic per
   // row (non-negative floats order as their bit patterns)
   float nvr = nvmax;
@@ -613,14 +590,14 @@ __global__ __launch_bounds__(64 * kLw) void k_ladder_decode(LadderDecodeArgs p) 
     const int hh = lane >> 3, w = lane & 7;
     const float mv = wst[0][hh][w], lv = wst[1][hh][w];
     const int ew = wexp[w];
-    float M = fmaxf(mv, dpp8<0xB1>(mv));
-    M = fmaxf(M, dpp8<0x4E>(M));
-    M = fmaxf(M, dpp8<0x141>(M));
+    float M = fmaxf(mv, fdpp<0xB1>(mv));
+    M = fmaxf(M, fdpp<0x4E>(M));
+    M = fmaxf(M, fdpp<0x141>(M));
     const bool some = mv != -__builtin_inff();
     float L = some ? lv * __builtin_amdgcn_exp2f(mv - M) : 0.0f;
-    L += dpp8<0xB1>(L);
-    L += dpp8<0x4E>(L);
-    L += dpp8<0x141>(L);
+    L += fdpp<0xB1>(L);
+    L += fdpp<0x4E>(L);
+    L += fdpp<0x141>(L);
     if (wave == 0 && w == 0 && !kOne) {
       rec[hh] = M;
       rec[8 + hh] = L;
