@@ -785,18 +785,15 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
     const int hh = lane >> 3, w = lane & 7;
     const float mv = wst[0][hh][w], lv = wst[1][hh][w];
     const int ew = wexp[w];
-    auto quad1 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xf, 0xf, false)); };
-    auto quad2 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x4E, 0xf, 0xf, false)); };
-    // the mirror of eight lanes: from any lane of one quad to one of the other, whose lanes agree by then
-    auto mirror8 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x141, 0xf, 0xf, false)); };
-    float M = fmaxf(mv, quad1(mv));
-    M = fmaxf(M, quad2(M));
-    M = fmaxf(M, mirror8(M));
+    // 0x141, the mirror of eight lanes: from any lane of one quad to one of the other, whose lanes agree by then
+    float M = fmaxf(mv, fdpp<0xB1>(mv));
+    M = fmaxf(M, fdpp<0x4E>(M));
+    M = fmaxf(M, fdpp<0x141>(M));
     const bool some = mv != -__builtin_inff();
     float L = some ? lv * fast_exp2(mv - M) : 0.0f;
-    L += quad1(L);
-    L += quad2(L);
-    L += mirror8(L);
+    L += fdpp<0xB1>(L);
+    L += fdpp<0x4E>(L);
+    L += fdpp<0x141>(L);
     if (wave == 0 && w == 0 && !kOne) {
       rec[hh] = M;
       rec[8 + hh] = L;
@@ -808,7 +805,8 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int u = 0; u < kDecWaves; ++u) fw[i][u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(f, 8 * (h0 + i) + u));
+        for (int u = 0; u < kDecWaves; ++u)
+          fw[i][u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(f, 8 * (h0 + i) + u));
     }
   }
   // rows summed over the waves -> A tile [head][128 m + k] (fp16). Audio and video rows are there for every
