@@ -134,10 +134,11 @@ __device__ __forceinline__ void value_inputs(const WindowArgs& a, size_t seq, in
   wmod = wfresh ? wm : 3u;
 }
 
-// The work-group's ticket, taken by its last thread: by then the lengths are in registers, so the work-group
-// that takes the last one may advance them. Taken where the row loads have been consumed, so that the
-// counter's round trip (and its turn: 11.5 ns a work-group, one after another) runs beside the rest of
-// the codes instead of after them.
+// The work-group's ticket, taken by its last thread. A barrier has to come first: the work-group that takes the
+// last ticket advances the lengths, so every wave here, not only the last one, must have its copy of them in
+// registers. Taken after the first barrier, where the row loads have been consumed, so that the counter's round
+// trip (and its turn: 11.5 ns a work-group, one after another) runs beside the rest of the codes instead of
+// after them.
 __device__ __forceinline__ void take_ticket(const WindowArgs& a, int tid, uint32_t& ticket) {
   uint32_t* p = a.ticket;
   __asm__ volatile("" : "+v"(p));  // per lane: of a uniform counter the compiler makes a wave-wide sum, and waits for it
@@ -352,8 +353,8 @@ __global__ __launch_bounds__(kThreads) void k_append_window(WindowArgs a) {
     __syncthreads();  // B0 (the waves of a work-group start together)
   }
   const int w0 = (begin / kW) * kW + kW * wi;  // the work-group's window
-  // the lengths are in registers from here on (and are not read again): the ticket may be taken
-  __asm__ volatile("" ::"s"(begin), "s"(len) : "memory");
+  // this wave's copy of the lengths is in registers from here on (and is not read again)
+  __asm__ volatile("; okvq: lengths read" ::"s"(begin), "s"(len) : "memory");
   uint32_t ticket;  // of the last thread only (no other value is joined with it, so nothing waits for it here)
   if (len > begin && w0 < len) {  // uniform
     if (values)
@@ -361,6 +362,7 @@ __global__ __launch_bounds__(kThreads) void k_append_window(WindowArgs a) {
     else
       key_window<kMeta>(a, sh, seq, begin, len, wi, tid, ticket);
   } else {
+    __syncthreads();  // every wave has read the lengths (it finds no window in them either)
     take_ticket(a, tid, ticket);
   }
 
