@@ -731,7 +731,7 @@ static okvq_status decode_impl(const okvq_cache* cache, const int32_t* lens_host
   }
   if (use_scratch) {  // the records of this call's plan, in the static array
     const size_t nsplit = is_ladder(&d) ? plan_ladder(d.batch, d.num_kv_heads, max_len).nsplit
-                                        : plan_decode(d.batch, d.num_kv_heads, std::max(max_len - d.residual, 0)).nsplit;
+                                        : plan_decode(d.batch, d.num_kv_heads, std::max(max_len - d.residual, 0), d.residual != 0).nsplit;
     if ((size_t)d.batch * d.num_kv_heads * nsplit * kRecFloats * sizeof(float) > OKVQ_NOALLOC_SCRATCH_BYTES)
       return OKVQ_ERR_WORKSPACE;
     st = scratch_address(&workspace);
@@ -776,7 +776,7 @@ static okvq_status decode_impl(const okvq_cache* cache, const int32_t* lens_host
                                            static_cast<hipStream_t>(stream), events ? ev : nullptr));
   }
   // with the fp16 residual the split-K launch covers the tokens below L - 128
-  const DecodePlan plan = plan_decode(d.batch, d.num_kv_heads, std::max(max_len - d.residual, 0));
+  const DecodePlan plan = plan_decode(d.batch, d.num_kv_heads, std::max(max_len - d.residual, 0), d.residual != 0);
   const Codebook& cb = codebook();
   const uint32_t cb01 = cb.level16[0] | ((uint32_t)cb.level16[1] << 16);
   const uint32_t cb23 = cb.level16[2] | ((uint32_t)cb.level16[3] << 16);

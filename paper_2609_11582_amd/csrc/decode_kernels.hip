@@ -52,7 +52,9 @@ constexpr int kAccPitch = 28;                   // combine tile [channel][24 row
 constexpr int kMinWps = 2 * kDecWaves;          // fewest windows per split (a pair per wave)
 // Sequences of at most this many windows take one split, whose work-group writes the output rows itself: a
 // second window pair per wave costs less than the merge launch (1024 tokens 11.8 -> 10.4 us, 512 tokens
-// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8).
+// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8). Not with the fp16
+// residual, whose tail needs the merge launch anyway: there a second split only helps (4 heads, 1152 tokens, 1024 of them in the
+// splits: 15.8 us with one, 13.6 with two).
 constexpr int kOneSplitWins = 32;
 constexpr float kLazy = 8.0f;                   // log2 headroom of the lazily updated softmax max
 
@@ -1273,13 +1275,14 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const f
   }
 }
 
-DecodePlan plan_decode(int B, int H, int max_len) {
+DecodePlan plan_decode(int B, int H, int max_len, bool tail) {
   const int nwin = (max_len + kW - 1) / kW;
   const long units = (long)B * H;
   long target_groups = 256;  // one work-group per compute unit
-  if (const char* env = getenv("OKVQ_DECODE_GROUPS")) target_groups = std::max(1L, atol(env));
+  const char* env = getenv("OKVQ_DECODE_GROUPS");  // a forced number of groups (tests, timing)
+  if (env) target_groups = std::max(1L, atol(env));
   int wps = (int)((nwin * units + target_groups - 1) / target_groups);
-  if (nwin <= kOneSplitWins) wps = std::max(wps, nwin);
+  if (nwin <= kOneSplitWins && !tail && !env) wps = std::max(wps, nwin);
   wps = std::max(wps, kMinWps);
   wps = std::max(wps, (nwin + kMaxSplits - 1) / kMaxSplits);
   wps = (wps + 1) / 2 * 2;  // whole window pairs

@@ -250,10 +250,11 @@ __global__ __launch_bounds__(64 * kDnWaves) void k_decode_dense(DenseArgs p) {
 DensePlan plan_dense(int B, int H, int max_len) {
   const long units = (long)B * H;
   long target_groups = 256;  // one work-group per compute unit (the value tiles take 128 KiB of LDS)
-  if (const char* env = getenv("OKVQ_DENSE_GROUPS")) target_groups = std::max(1L, atol(env));
+  const char* env = getenv("OKVQ_DENSE_GROUPS");  // a forced number of groups (tests, timing)
+  if (env) target_groups = std::max(1L, atol(env));
   long tps = ((long)max_len * units + target_groups - 1) / target_groups;
   // one split, without a merge launch, up to two steps: 512 tokens 8.8 -> 7.7 us, 768 tokens 9.5 against 10.2
-  if (max_len <= 2 * kDnStep) tps = std::max(tps, (long)max_len);
+  if (max_len <= 2 * kDnStep && !env) tps = std::max(tps, (long)max_len);
   tps = std::max(tps, (long)kDnStep);
   tps = std::max(tps, ((long)max_len + kMaxSplits - 1) / kMaxSplits);
   tps = (tps + kDnStep - 1) / kDnStep * kDnStep;  // whole work-group steps

@@ -178,7 +178,9 @@ struct DecodePlan {
   int wins_per_split;  // 32-token windows per split-K work-group
   int nsplit;          // splits per (sequence, KV head)
 };
-DecodePlan plan_decode(int B, int H, int max_len);
+// max_len: the longest sequence, without the tail left to the merge launch; tail: there is one (the fp16
+// residual), so that one split per sequence would not save that launch
+DecodePlan plan_decode(int B, int H, int max_len, bool tail);
 size_t decode_workspace_bytes(int B, int H, int Hq, int max_len);
 hipError_t launch_prepare_rotation(const float* rot, uint16_t* rot16t, hipStream_t s);
 // events: nullptr, or four events bound to the launches: split-K start, end; merge start, end
