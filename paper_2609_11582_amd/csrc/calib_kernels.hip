@@ -21,6 +21,8 @@
 //                     fp16 hi + lo parts, B = v), one partial per (run, modality);
 //  k_calib_reduce     C_m = the sum of the partials, in a fixed order.
 #include <algorithm>
+#include <cfloat>
+#include <cmath>
 
 #include "launch.hpp"
 
@@ -400,7 +402,11 @@ size_t calib_workspace_bytes(int B, int H, int Hq, int N) {
 
 hipError_t launch_calib_weights(const uint16_t* q, const uint16_t* k, const LenArgs& lens, int b0, int nb, int N,
                                 int H, int Hq, float sm_scale, float* w, void* ws, hipStream_t s) {
-  const float scale2 = sm_scale * 1.4426950408889634f;
+  // Masked scores are -inf before the scale, so the scale may not be zero (-inf 0 is NaN). The least normal number
+  // stands for everything below it, with the same result: a score is less than 2^39 (128 products of fp16 values),
+  // so that it scales to less than 2^-87, whose power of two rounds to 1.
+  float scale2 = sm_scale * 1.4426950408889634f;
+  if (std::fabs(scale2) < FLT_MIN) scale2 = FLT_MIN;
   float2* stats = static_cast<float2*>(ws);
   const long groups = (long)((N + kCalGroup - 1) / kCalGroup) * Hq * nb;
   if (groups > INT32_MAX) return hipErrorInvalidValue;

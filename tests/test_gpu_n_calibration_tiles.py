@@ -40,3 +40,26 @@ def test_weights_and_covariance_at_tile_edges(lens, H, Hq, sign):
     want = value_covariance(v, mod, got, lens)
     scale = value_covariance(np.abs(v.astype(np.float64)), mod, got, lens)
     assert np.all(np.abs(cov.cpu().numpy() - want) <= 1e-5 * scale + 1e-30)
+
+
+@pytest.mark.parametrize("sm", [0.0, -0.0, 1e-45, -1e-39])
+def test_weights_at_scale_zero(sm):
+    """A zero scale (and one that underflows) attends every earlier key alike: w_t is the sum over the group's
+    heads and the positions i >= t of 1 / (i + 1)^2. The same bounds."""
+    import torch
+
+    import gpu_helpers as gh
+    import paper_2609_11582_amd as okvq
+    rng = np.random.default_rng(5)
+    lens, H, Hq = [1, 33, 130, 0, 200], 2, 6
+    B, N = len(lens), max(lens)
+    q = rng.standard_normal((B, Hq, N, 128)).astype(np.float16)
+    k = rng.standard_normal((B, H, N, 128)).astype(np.float16)
+    q[4], k[4] = 60000 * np.sign(q[4]), 60000 * np.sign(k[4])  # the largest scores
+    print(f"[gpu-case] calibration weights scale={sm}", flush=True)
+    dims = okvq.make_dims(B, H, Hq, 32)
+    w = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
+    okvq.okvq_calibration_weights(dims, gh.f16dev(q), gh.f16dev(k), N, lens, sm, w, okvq.calibration_workspace(dims, N))
+    torch.cuda.synchronize()
+    got, ref = w.cpu().numpy().astype(np.float64), attention_weights(q, k, lens, 0.0)
+    assert np.all(np.abs(got - ref) <= 3e-4 * ref + 1e-7 * ref.max())
