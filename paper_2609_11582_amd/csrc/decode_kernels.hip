@@ -52,9 +52,9 @@ constexpr int kAccPitch = 28;                   // combine tile [channel][24 row
 constexpr int kMinWps = 2 * kDecWaves;          // fewest windows per split (a pair per wave)
 // Sequences of at most this many windows take one split, whose work-group writes the output rows itself: a
 // second window pair per wave costs less than the merge launch (1024 tokens 11.8 -> 10.4 us, 512 tokens
-// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8). Not with the fp16
-// residual, whose tail needs the merge launch anyway: there a second split only helps (4 heads, 1152 tokens, 1024 of them in the
-// splits: 15.8 us with one, 13.6 with two).
+// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8). Not with the fp16 residual,
+// whose tail needs the merge launch anyway: there a second split only helps (4 heads, 1152 tokens, 1024 of
+// them in the splits: 15.8 us with one, 13.6 with two).
 constexpr int kOneSplitWins = 32;
 constexpr float kLazy = 8.0f;                   // log2 headroom of the lazily updated softmax max
 
@@ -1035,9 +1035,12 @@ struct TailArgs {
 // A wave's 32 ring slots are scored, weighted and summed by that wave alone, in the frame of its own maximum, so
 // that the work-group meets twice: once for the query tables, once for the last sum. Scores run on mixed fp16 /
 // fp32 multiply-adds against tables that hold q' step 2^(24 - shift) (the codes enter as fp16 subnormals, as
-// in the split kernel) and the windows' q'.m once, not per token. Ring rows are taken by slot, whatever the length,
-// so that their loads do not wait for it. Bound by its chain (length, codes, tables, scores, outputs): 28 heads
-// over 64 splits took 6.8 us, 1.45 of it for the scores, 1.2 for the groups' two barriers; now 5.5.
+// in the split kernel) and the windows' q'.m once, not per token. Value rows are taken by slot, whatever the length,
+// so that their loads do not wait for it; key rows wait, because those of quantized keys (half of the tail on
+// average, all of it at multiples of 128 tokens) are bytes for nothing: read as well, they made a call of 512
+// heads at 512 tokens 18.6 us instead of 14.9, and one of 28 heads 13.5 instead of 13.0. Bound by its chain
+// (length, codes, tables, scores, outputs): 28 heads over 64 splits took 6.8 us, 1.45 of it for the scores, 1.2
+// for the groups' two barriers; now 5.5.
 constexpr int kTabHalf = 68, kTabRow = 2 * kTabHalf;  // table pitches: a wave's broadcast reads hit distinct banks
 
 __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const float* __restrict__ ws, int H, int Hq,
@@ -1058,8 +1061,8 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const f
   const size_t seq = (size_t)b * H + h;
   const float* base = ws + seq * nsplit * kRecFloats;
 
-  // ---- every load goes out before any is used: first what needs no length (split records, the query, the ring
-  // rows), then the tail's codes, norms and metadata ----
+  // ---- every load goes out before any is used: first what needs no length (split records, the query, the value
+  // rows), then the tail's raw keys, codes, norms and metadata ----
   const int len_dev = ta.seq_lens[b];  // first, a scalar load in flight while the records' loads go out
   SplitChunk ch0;
   if (sg < nsplit) load_split_chunk(base, nsplit, hd, q4, sg, ch0);
@@ -1068,12 +1071,6 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const f
   const uint32_t s4 = *reinterpret_cast<const uint32_t*>(ta.signs + 4 * q4);
   // scores: two lanes per ring slot, channels 64 half .. 64 half + 63
   const int slot = 32 * wave + (lane >> 1), half = lane & 1;
-  uint4 kr[8];
-  {
-    const uint4* row = reinterpret_cast<const uint4*>(ta.k_res + (seq * kResidual + slot) * kD + 64 * half);
-#pragma unroll
-    for (int u = 0; u < 8; ++u) kr[u] = row[u];
-  }
   // outputs: channel octet c8 of the eight slots whose weights lie in the lane's row of 16 (every ring row is
   // finite; slots past the tail get weight 0)
   const int c8 = lane & 15;
@@ -1090,6 +1087,12 @@ __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const f
   const int w0 = T0 / kW, nwq = (Kq > T0) ? (Kq - 1) / kW - w0 + 1 : 0;
   const int ti = T0 + ((slot - T0) & (kResidual - 1));  // the slot's token
   const bool tok = ti < L, quant = tok && ti < Kq;
+  uint4 kr[8];
+  {  // the slot's key row, or ring row 0 for a quantized key (one shared row, never used)
+    const uint4* row = reinterpret_cast<const uint4*>(ta.k_res + (seq * kResidual + (quant ? 0 : slot)) * kD + 64 * half);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) kr[u] = row[u];
+  }
   const int tc = min(ti, ta.cap - 1);
   const uint4 kq = *reinterpret_cast<const uint4*>(ta.k_codes + (seq * ta.cap + tc) * 32 + 16 * half);
   const uint32_t knrm = ta.k_norm[seq * ta.cap + tc];
