@@ -680,11 +680,14 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
     ring_wait<kMeta>(hi - k);
     // The two waves of a SIMD are w and w + 4, and the older one wins every issue: it finished 2-4 us before
     // the other, which then ran alone. The younger one leads in every second of its rounds, counted from the
-    // last, where the older one leads again (so a split of one round is as before): 16 ragged sequences of up
-    // to 12288 tokens with MXFP4 metadata 29.1 -> 26.9 us, 131072 tokens 18.9 -> 18.5. (Younger first in
-    // every round: 28.7 and 19.7, and 32768 tokens 12.4 -> 13.5.)
+    // last, where the older one leads again: 16 sequences of 16384 tokens and 4 heads with MXFP4 metadata 29.4 ->
+    // 27.1 us, fp16 27.8 -> 25.9, 131072 tokens 19.3 -> 18.9, and 1024 tokens in one split of two rounds 10.5 ->
+    // 10.3. Among several splits not where they have three rounds or fewer (64 sequence heads of 5000 tokens with
+    // MXFP4 metadata 16.2 -> 15.7 us without) and not over TurboQuant keys, whose rounds read no metadata (16
+    // sequence heads of 32768 tokens 18.8 -> 17.8 without). (Younger first in every round: 131072 tokens 19.7,
+    // and 32768 tokens 12.4 -> 13.5.)
     const int rounds = (w_end - wA + 2 * kDecWaves - 1) / (2 * kDecWaves);  // left, with this one
-    if (wave >= kDecWaves / 2 && !(rounds & 1))
+    if (wave >= kDecWaves / 2 && !(rounds & 1) && (kOne || (!kTq && p.wps > 6 * kDecWaves)))
       __builtin_amdgcn_s_setprio(1);
     else
       __builtin_amdgcn_s_setprio(0);
