@@ -878,14 +878,15 @@ okvq_status okvq_value_covariance(const okvq_dims* dims, const uint16_t* v, cons
       workspace_bytes < calib_workspace_bytes(dims->batch, dims->num_kv_heads, dims->num_q_heads, n_tokens))
     return OKVQ_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int H = dims->num_kv_heads, nrun = calib_covariance_runs(n_tokens);
+  const int H = dims->num_kv_heads, run = calib_covariance_run(dims->batch, H, n_tokens);
+  const int nrun = calib_covariance_runs(run, n_tokens);
   const int nparts = dims->batch * H * nrun;
   for (int b0 = 0; b0 < dims->batch; b0 += kMaxLenArgs) {
     const int nb = std::min(kMaxLenArgs, dims->batch - b0);
     LenArgs la{};
     for (int i = 0; i < nb; ++i) la.lens[i] = lens_host[b0 + i];
     const bool last = b0 + nb >= dims->batch;
-    st = hip_status(launch_calib_covariance(v, modality, w, la, b0, nb, n_tokens, H, static_cast<float*>(workspace),
+    st = hip_status(launch_calib_covariance(v, modality, w, la, b0, nb, n_tokens, H, run, static_cast<float*>(workspace),
                                             b0 * H * nrun, cov, last, nparts, s));
     if (st != OKVQ_OK) return st;
   }

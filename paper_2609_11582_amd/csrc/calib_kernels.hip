@@ -259,20 +259,22 @@ __global__ __launch_bounds__(256) void k_calib_groupsum(const float* __restrict_
 }
 
 // ---- weighted covariance partials. Grid (runs of chunks, 2 H, sequences): a work-group takes
-// kCovRun chunks of 64 tokens of one (sequence, KV head) and the output rows 64 half .. + 63, and writes
+// run_chunks chunks of 64 tokens of one (sequence, KV head) and the output rows 64 half .. + 63, and writes
 // partial[((bz H + h) nrun + run) 3 + m][c1][c2] = sum over the run's tokens t of modality m of w_t
 // v_t[c1] v_t[c2]. A chunk is staged channel-major in LDS: v (fp16) and, for the work-group's rows, the hi
 // / lo fp16 parts of w v; the next chunk's rows are loaded while it is used. Wave w accumulates the 16
 // rows 16 w .. of the three modalities in registers over the whole run, so that the partials written
-// here and read by the reduction are 1 / kCovRun of the chunks'. Bound by the partials' traffic: two
+// here and read by the reduction are 1 / run_chunks of the chunks'. Bound by the partials' traffic: two
 // chunks a run still give a work-group per compute unit at 4096 tokens and 4 heads, and 11.9 + 17.2 us
-// for the two kernels became 11.7 + 5.8 us (four: 16.4 + 5.0 us) ----
-constexpr int kCovRun = 2;   // chunks per work-group
+// for the two kernels became 11.7 + 5.8 us (four: 16.4 + 5.0 us). With fewer than 64 chunks in all the second
+// chunk's chain is what the call takes, not the traffic: one a run (500 tokens, one head 11.7 -> 9.3 us a
+// call, 4 heads 13.0 -> 11.8; at 64 chunks two a run take 14.6 us against 15.1) ----
+constexpr int kCovShort = 64;
 constexpr int kCovRows = kD / 2;  // output rows per work-group
 __global__ __launch_bounds__(kCalThreads) void k_calib_covariance(const uint16_t* __restrict__ v,
                                                                   const uint8_t* __restrict__ modality,
                                                                   const float* __restrict__ w, LenArgs lens, int b0,
-                                                                  int N, int H, int nrun,
+                                                                  int N, int H, int nrun, int run_chunks,
                                                                   float* __restrict__ partial) {
   __shared__ __attribute__((aligned(16))) _Float16 vt[kD][kCovChunk + 8];         // v[t][c] at [c][t]
   __shared__ __attribute__((aligned(16))) _Float16 whi[kCovRows][kCovChunk + 8];  // fp16(w v)
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(kCalThreads) void k_calib_covariance(const uint16_t
   for (int m = 0; m < 3; ++m)
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) acc[m][cb] = c_floatx4{0.f, 0.f, 0.f, 0.f};
-  const int c0 = run * kCovRun, c1 = min(c0 + kCovRun, (L + kCovChunk - 1) / kCovChunk);
+  const int c0 = run * run_chunks, c1 = min(c0 + run_chunks, (L + kCovChunk - 1) / kCovChunk);
   if (c0 < c1) load(c0);
   for (int chunk = c0; chunk < c1; ++chunk) {
     if (chunk > c0) __syncthreads();  // every wave is done with the previous chunk
@@ -423,14 +425,17 @@ hipError_t launch_calib_weights(const uint16_t* q, const uint16_t* k, const LenA
   return hipGetLastError();
 }
 
-int calib_covariance_runs(int N) { return (N + kCovRun * kCovChunk - 1) / (kCovRun * kCovChunk); }
+int calib_covariance_run(int B, int H, int N) {
+  return (int64_t)B * H * ((N + kCovChunk - 1) / kCovChunk) < kCovShort ? 1 : 2;
+}
+int calib_covariance_runs(int run_chunks, int N) { return (N + run_chunks * kCovChunk - 1) / (run_chunks * kCovChunk); }
 
 hipError_t launch_calib_covariance(const uint16_t* v, const uint8_t* modality, const float* w, const LenArgs& lens,
-                                   int b0, int nb, int N, int H, float* partial, int part0, float* cov, bool reduce,
-                                   int nparts_total, hipStream_t s) {
-  const int nrun = calib_covariance_runs(N);
+                                   int b0, int nb, int N, int H, int run_chunks, float* partial, int part0, float* cov,
+                                   bool reduce, int nparts_total, hipStream_t s) {
+  const int nrun = calib_covariance_runs(run_chunks, N);
   hipLaunchKernelGGL(k_calib_covariance, dim3(nrun, 2 * H, nb), dim3(kCalThreads), 0, s, v, modality, w, lens, b0, N, H,
-                     nrun, partial + (size_t)part0 * 3 * kD * kD);
+                     nrun, run_chunks, partial + (size_t)part0 * 3 * kD * kD);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !reduce) return e;
   hipLaunchKernelGGL(k_calib_reduce, dim3(3 * kD * kD / 256), dim3(256), 0, s, static_cast<const float*>(partial),

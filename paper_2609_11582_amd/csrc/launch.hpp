@@ -126,9 +126,10 @@ size_t calib_workspace_bytes(int B, int H, int Hq, int N);
 hipError_t launch_calib_weights(const uint16_t* q, const uint16_t* k, const LenArgs& lens, int b0, int nb, int N,
                                 int H, int Hq, float sm_scale, float* w, void* ws, hipStream_t s);
 hipError_t launch_calib_covariance(const uint16_t* v, const uint8_t* modality, const float* w, const LenArgs& lens,
-                                   int b0, int nb, int N, int H, float* partial, int part0, float* cov, bool reduce,
-                                   int nparts_total, hipStream_t s);
-int calib_covariance_runs(int N);  // covariance partials per (sequence, KV head)
+                                   int b0, int nb, int N, int H, int run_chunks, float* partial, int part0, float* cov,
+                                   bool reduce, int nparts_total, hipStream_t s);
+int calib_covariance_run(int B, int H, int N);         // chunks per covariance partial
+int calib_covariance_runs(int run_chunks, int N);      // covariance partials per (sequence, KV head)
 
 struct CacheView {
   int B, H, Hq, cap;

@@ -63,3 +63,26 @@ def test_weights_at_scale_zero(sm):
     torch.cuda.synchronize()
     got, ref = w.cpu().numpy().astype(np.float64), attention_weights(q, k, lens, 0.0)
     assert np.all(np.abs(got - ref) <= 3e-4 * ref + 1e-7 * ref.max())
+
+
+@pytest.mark.parametrize("lens,H", [([64, 65, 0], 1), ([4031], 1), ([4033], 1), ([129, 2000], 2)])
+def test_covariance_runs_of_one_and_two_chunks(lens, H):
+    """Fewer than 64 chunks of 64 tokens (over sequences and heads) take one chunk a partial, more take two; the
+    first and last of each kind, with odd chunk counts. The same bound as above."""
+    import torch
+
+    import gpu_helpers as gh
+    import paper_2609_11582_amd as okvq
+    rng = np.random.default_rng(sum(lens))
+    B, N = len(lens), max(lens)
+    v = rng.standard_normal((B, H, N, 128)).astype(np.float16)
+    w = rng.random((B, H, N)).astype(np.float32)
+    mod = rng.integers(0, 3, (B, N)).astype(np.uint8)
+    print(f"[gpu-case] covariance runs lens={lens} H={H}", flush=True)
+    dims = okvq.make_dims(B, H, H, 32)
+    cov = torch.full((3, 128, 128), float("nan"), dtype=torch.float32, device="cuda")
+    okvq.okvq_value_covariance(dims, gh.f16dev(v), gh.dev(mod), gh.dev(w), N, lens, cov, okvq.calibration_workspace(dims, N))
+    torch.cuda.synchronize()
+    want = value_covariance(v, mod, w.astype(np.float64), lens)
+    scale = value_covariance(np.abs(v.astype(np.float64)), mod, w.astype(np.float64), lens)
+    assert np.all(np.abs(cov.cpu().numpy() - want) <= 1e-5 * scale + 1e-30)
