@@ -25,6 +25,9 @@
 // after another (8 us of the 39 us of a 32768-token, 4-head prefill with 1024 work-groups), the launch
 // 2.5 us.
 //
+// Stateless 2-bit values have no prepared fragments of R_m, only the fp32 matrix, which every work-group converts:
+// large calls take wider units (k_values_wide below).
+//
 // Bound by VALU issue (keys about 20 operations a channel, values about 8) at four waves per SIMD. 32768
 // tokens, 4 KV heads: 38.7 -> 29.1 us a call for the 2-bit layout (the tile codec: two waves per SIMD), 73 ->
 // 32 us at 3 bits (separate key and value kernels, which converted R_m in every work-group).
@@ -412,14 +415,15 @@ __device__ __forceinline__ void key_unit(const BlockArgs& a, KeyShared& sh, cons
 // ------------------------------------------------------------------------------------------------
 // Values
 // ------------------------------------------------------------------------------------------------
-// The wave's slice of R_m as MFMA operands: bf[i][kk][part] for output block 2 v + i, k-block kk, part 0 =
+// The wave's slice of R_m as MFMA operands: bf[i][kk][part] for output block kNb v + i, k-block kk, part 0 =
 // fp16(R) and 1 = fp16(R - fp16(R)); from the prepared fragments, or converted from the fp32 matrix.
-__device__ __forceinline__ void load_rot_slice(const BlockArgs& a, int m, int v, int lane, uint4 (&bf)[2][4][2]) {
-  if (a.rotfrag) {
-    const char* base = reinterpret_cast<const char*>(a.rotfrag) + (size_t)(m * 8 + 2 * v) * 8 * 1024;
+template <int kNb>
+__device__ __forceinline__ void load_rot_slice(const BlockArgs& a, int m, int v, int lane, uint4 (&bf)[kNb][4][2]) {
+  if (kNb > 1 && a.rotfrag) {  // (one block a wave: only without fragments)
+    const char* base = reinterpret_cast<const char*>(a.rotfrag) + (size_t)(m * 8 + kNb * v) * 8 * 1024;
     const uint32_t off = 16u * (uint32_t)lane;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < kNb; ++i)
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
@@ -429,10 +433,10 @@ __device__ __forceinline__ void load_rot_slice(const BlockArgs& a, int m, int v,
   }
   const int r = lane & 15, g = lane >> 4;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < kNb; ++i)
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
-      const float4* p = reinterpret_cast<const float4*>(a.rot + ((size_t)(m * kD + 16 * (2 * v + i) + r)) * kD + 32 * kk + 8 * g);
+      const float4* p = reinterpret_cast<const float4*>(a.rot + ((size_t)(m * kD + 16 * (kNb * v + i) + r)) * kD + 32 * kk + 8 * g);
       const float4 f0 = p[0], f1 = p[1];
       const float fv[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
       half8 hv, lv;
@@ -489,6 +493,40 @@ __device__ __forceinline__ uint32_t xor32(uint32_t v, int g) {
   uint32_t a = v, b = v;
   __asm__("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
   return (g & 2) ? a : b;
+}
+
+// Sum of squares of the rows of two row blocks in LDS (lane l: row l % 16 of block l / 32) by the halving tree: levels
+// 64 and 32 in the lane, 16 and 8 across lane groups (the first by a row swap that leaves block 0 in lanes 0-31
+// and block 1 in lanes 32-63)
+__device__ __forceinline__ float row_squares(const uint4 (&rows0)[4][64], const uint4 (&rows1)[4][64], int lane) {
+  float p[2][8];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {
+    half8 xv[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) xv[kk] = as_half8((rb ? rows1 : rows0)[kk][lane]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      // squares of fp16 values are exact; as fma (mixed precision) they need no conversion of their own
+      const float f0 = (float)xv[0][e], f1 = (float)xv[1][e], f2 = (float)xv[2][e], f3 = (float)xv[3][e];
+      const float l0 = __builtin_fmaf(f0, f0, __builtin_fmaf(f2, f2, 0.0f));
+      const float l1 = __builtin_fmaf(f1, f1, __builtin_fmaf(f3, f3, 0.0f));
+      p[rb][e] = l0 + l1;
+    }
+  }
+  float s[8], z[8];
+  swap_halves(p[0], p[1]);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) z[e] = s[e] = p[0][e] + p[1][e];
+  swap_rows(s, z);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s[e] = s[e] + z[e];
+#pragma unroll
+  for (int n = 4; n >= 1; n >>= 1) {
+#pragma unroll
+    for (int e = 0; e < n; ++e) s[e] = s[e] + s[e + n];
+  }
+  return s[0];
 }
 
 // Codes of the lane's four channels 16 nb + 4 g .. + 3 of its token as a 4 b-bit field
@@ -590,36 +628,8 @@ __device__ __forceinline__ void value_unit(const BlockArgs& a, ValueShared& sv, 
   if (rows) {
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's rows have landed
 
-    // ---- fp16 norms by the halving tree: levels 64 and 32 in the lane, 16 and 8 across lane groups (the
-    // first by a row swap that leaves row block 0 in lanes 0-31 and row block 1 in lanes 32-63) ----
-    float p[2][8];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-      half8 xv[4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) xv[kk] = as_half8(sv.rows[2 * v + rb][kk][lane]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        // squares of fp16 values are exact; as fma (mixed precision) they need no conversion of their own
-        const float f0 = (float)xv[0][e], f1 = (float)xv[1][e], f2 = (float)xv[2][e], f3 = (float)xv[3][e];
-        const float l0 = __builtin_fmaf(f0, f0, __builtin_fmaf(f2, f2, 0.0f));
-        const float l1 = __builtin_fmaf(f1, f1, __builtin_fmaf(f3, f3, 0.0f));
-        p[rb][e] = l0 + l1;
-      }
-    }
-    float s[8], z[8];
-    swap_halves(p[0], p[1]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = s[e] = p[0][e] + p[1][e];
-    swap_rows(s, z);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s[e] = s[e] + z[e];
-#pragma unroll
-    for (int n = 4; n >= 1; n >>= 1) {
-#pragma unroll
-      for (int e = 0; e < n; ++e) s[e] = s[e] + s[e + n];
-    }
-    const uint32_t n16 = fresh ? norm_to_f16(sqrt_rn(s[0])) : 0u;
+    const float sq = row_squares(sv.rows[2 * v], sv.rows[2 * v + 1], lane);
+    const uint32_t n16 = fresh ? norm_to_f16(sqrt_rn(sq)) : 0u;
     // 3: no code; with the global rotation every coded token takes R_0. (The ladder codes a zero row too:
     // its code is that of y = 0 against zero thresholds.)
     const uint32_t mt = (fresh && mymod <= 2u && (kLadder || n16 != 0)) ? (a.global_rot ? 0u : mymod) : 3u;
@@ -740,7 +750,102 @@ __device__ __forceinline__ void value_unit(const BlockArgs& a, ValueShared& sv, 
       dst[4] = (uint16_t)w1;
     }
   }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Stateless 2-bit values from the fp32 matrix: units of 256 tokens on eight waves, one output block of 16 channels
+// each, so that every slice of R_m is converted once for 256 tokens, at the same four waves per SIMD. A lane's code
+// bytes (one per window and row block) meet in LDS, where the rows were, and leave 16 bytes a lane. Bound by the
+// conversion (8.4 of 25.5 us in units of 128 tokens, where prepared fragments would take 17.1) and the matrix
+// products: 32768 tokens of 4 heads 25.5 -> 20.6 us, 131072 tokens 82.7 -> 66.7.
+constexpr int kWideUnit = 256, kWideWaves = 8;
+struct WideShared {
+  uint4 rows[kWideUnit / 16][4][64];
+  float nrm[kWideUnit];
+  uint8_t ktab[3][kWideUnit / 4];
+  uint32_t present[3][kWideWaves];
+};
+
+__global__ __launch_bounds__(64 * kWideWaves, 4) void k_values_wide(BlockArgs a) {
+  __shared__ __attribute__((aligned(16))) WideShared sv;
+  const Unit c = unit_at(a, blockIdx.x, a.val_nx, kWideUnit);
+  if (c.tok0 >= c.len) return;  // uniform
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wtok0 = c.tok0 + 32 * v;
+  const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)&sv.rows[2 * v][0][0]);
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb) {  // rows past the end repeat the last one (never coded)
+    const uint4* p = reinterpret_cast<const uint4*>(a.v + (c.seq * a.n_rows + min(wtok0 + 16 * rb + r, c.len - 1)) * kD) + g;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) dma16(p + 4 * kk, lds + (rb * 4 + kk) * 1024);
   }
+  const int mytok = wtok0 + 16 * (lane >> 5) + r;  // lane l: token 16 (l / 32) + l % 16 of the wave's 32
+  const bool fresh = mytok < c.len;
+  const uint32_t mymod = a.modality[(size_t)c.b * a.n_rows + min(mytok, c.len - 1)];
+  const int first_m = a.global_rot ? 0 : 1;
+  uint4 bf[1][4][2];
+  load_rot_slice(a, first_m, v, lane, bf);
+  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's rows have landed
+  const float sq = row_squares(sv.rows[2 * v], sv.rows[2 * v + 1], lane);
+  const uint32_t n16 = fresh ? norm_to_f16(sqrt_rn(sq)) : 0u;
+  const uint32_t mt = (fresh && mymod <= 2u && n16 != 0) ? (a.global_rot ? 0u : mymod) : 3u;
+  if ((g & 1) == 0) {
+    sv.nrm[32 * v + 16 * (lane >> 5) + r] = (n16 != 0) ? __builtin_amdgcn_rcpf(h2f(n16) * a.th.t2) : 0.0f;
+    if (mytok < (c.len + kW - 1) / kW * kW) a.v_norm[c.seq * a.cap + mytok] = (uint16_t)n16;
+  }
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    const uint64_t mb = __ballot(mt == (uint32_t)m);
+    if (lane < 8) {  // quad `lane` of the wave: its tokens' bits -> bits 2 i, 2 i + 1
+      const uint32_t b4 = (uint32_t)(mb >> (32 * (lane >> 2) + 4 * (lane & 3))) & 15u;
+      const uint32_t spread = (b4 & 1u) | ((b4 & 2u) << 1) | ((b4 & 4u) << 2) | ((b4 & 8u) << 3);
+      sv.ktab[m][8 * v + lane] = (uint8_t)(spread * 3u);
+    }
+    if (lane == 0) sv.present[m][v] = ((mb & 0xffffull) ? 1u << (2 * v) : 0u) | ((mb >> 32) ? 2u << (2 * v) : 0u);
+  }
+  __syncthreads();  // rows and tables complete
+  uint32_t vb[kWideUnit / 64] = {0u, 0u, 0u, 0u};  // byte i of word q: row block 4 q + i
+#pragma unroll 1
+  for (int mi = 0, m = first_m; mi < 3; ++mi, m = (m == 2) ? 0 : m + 1) {
+    const uint4 p0 = *reinterpret_cast<const uint4*>(&sv.present[m][0]), p1 = *reinterpret_cast<const uint4*>(&sv.present[m][4]);
+    const uint32_t rbs = __builtin_amdgcn_readfirstlane(p0.x | p0.y | p0.z | p0.w | p1.x | p1.y | p1.z | p1.w);
+    if (rbs == 0) continue;
+    if (m != first_m) load_rot_slice(a, m, v, lane, bf);
+#pragma unroll
+    for (int w = 0; w < kWideUnit / kW; ++w) {
+      if (!((rbs >> (2 * w)) & 3u)) continue;  // uniform
+      floatx4 y[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const half8 x0 = as_half8(sv.rows[2 * w][kk][lane]), x1 = as_half8(sv.rows[2 * w + 1][kk][lane]);
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+          y[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x0, as_half8(bf[0][kk][part]), y[0], 0, 0, 0);
+          y[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x1, as_half8(bf[0][kk][part]), y[1], 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {  // the same decision as above
+        const float4 it = *reinterpret_cast<const float4*>(&sv.nrm[16 * (2 * w + i) + 4 * g]);
+        const float iv[4] = {it.x, it.y, it.z, it.w};
+        uint32_t s0 = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s0 += (uint32_t)min(max(floor_i32(y[i][k] * iv[k]), -2), 1) << (2 * k);
+        vb[w / 2] |= ((s0 + 0xAAu) & (uint32_t)sv.ktab[m][4 * (2 * w + i) + g]) << (8 * (2 * (w & 1) + i));
+      }
+    }
+  }
+  __syncthreads();  // every wave is done with the rows
+  uint8_t* tile = reinterpret_cast<uint8_t*>(&sv.rows[0][0][0]);  // the unit's code bytes: [window][1024]
+#pragma unroll
+  for (int rb = 0; rb < kWideUnit / 16; ++rb)
+    tile[1024 * (rb >> 1) + 16 * lane + 8 * (rb & 1) + v] = (uint8_t)(vb[rb >> 2] >> (8 * (rb & 3)));
+  __syncthreads();
+  if (wtok0 < c.len)  // wave v: window v
+    *reinterpret_cast<uint4*>(a.v_codes + (c.seq * (a.cap / kW) + wtok0 / kW) * 1024 + 16 * lane) =
+        *reinterpret_cast<const uint4*>(tile + 1024 * v + 16 * lane);
+}
 
 // ------------------------------------------------------------------------------------------------
 // Work-groups n < 2 paired alternate between the roles in runs of kRun; the rest of the key units (half as
@@ -780,8 +885,18 @@ hipError_t launch_codec_block(const BlockArgs& args, int key_meta, bool keys, bo
                               hipEvent_t const* events) {
   if (args.nb <= 0 || span <= 0 || (!keys && !values)) return hipSuccess;
   BlockArgs a = args;
-  a.key_nx = std::max((span + kKeyUnit - 1) / kKeyUnit, 1);
   const int64_t per = (int64_t)a.H * a.nb;
+  // Stateless 2-bit values: wide units from 129 on. Up to 128 the 64-token units are at most two per compute unit,
+  // one round, and have the shorter chain (4 heads: 2048 tokens 9.1 us against 12.5, 8192 tokens 12.5 against 12.9);
+  // beyond, every round of theirs converts R_m again (9216 tokens 16.2 against 13.0, 65536 tokens 46.3 against 35.7).
+  const int64_t wide = per * ((span + kWideUnit - 1) / kWideUnit);
+  if (!keys && a.key_bits == 0 && !a.rotfrag && wide > 128) {
+    if (wide * 64 * kWideWaves > UINT32_MAX) return hipErrorInvalidValue;  // a launch holds fewer than 2^32 threads
+    a.val_nx = (span + kWideUnit - 1) / kWideUnit;
+    hipLaunchKernelGGL(k_values_wide, dim3((uint32_t)wide), dim3(64 * kWideWaves), 0, s, a);
+    return hipGetLastError();
+  }
+  a.key_nx = std::max((span + kKeyUnit - 1) / kKeyUnit, 1);
   // Half-size value units where whole ones would leave compute units with fewer than two: a unit's serial
   // chain is what such a launch takes (four 512-token chunks of 8 sequence heads, with their decode steps:
   // 127.5 -> 121.2 us), while a full chip pays for the second read of R_m (32768 tokens, 4 heads: 29.9 against

@@ -41,3 +41,34 @@ def test_block_and_window_codecs_write_the_tile_codecs_bytes(meta, residual, fla
         for name in want:
             a, b = got[name].view(np.uint8), want[name].view(np.uint8)
             assert np.array_equal(a, b), f"{path}, {name}: {int((a != b).sum())} bytes differ"
+
+
+@pytest.mark.parametrize("lens,heads,flags", [([33000], 1, 0), ([256, 255, 0], 64, 2), ([257, 1, 300], 33, 0),
+                                              ([1024, 993], 17, 0), ([256, 200], 64, 0)])
+def test_stateless_values_write_the_appended_bytes(lens, heads, flags):
+    """okvq_quantize_values from the fp32 matrix against the block codec's append from the prepared fragments: the
+    same split of R_m and the same order of products, so the same bytes. More than 128 units of 256 tokens take the
+    wide kernel (all but the last case, at 128), with lengths at, inside and past a unit's and a window's edge."""
+    import torch
+
+    import gpu_helpers as gh
+    import paper_2609_11582_amd as okvq
+    rng = np.random.default_rng(sum(lens) + heads)
+    wl = workload("omni3b_b4_64k_stream")
+    n, B = max(lens), len(lens)
+    lay = gen_layer(wl, 1, lengths=np.asarray([32], np.int32), n_tokens=32)
+    v = rng.standard_normal((B, heads, n, 128)).astype(np.float16)
+    v[:, :, :: 57] = 0
+    mod = rng.integers(0, 3, (B, n)).astype(np.uint8)
+    mod[:, n // 2:] = 1
+    cap = (n + 31) // 32 * 32
+    print(f"[gpu-case] stateless values lens={lens} heads={heads} flags={flags}", flush=True)
+    cache = okvq.KVCache(B, heads, heads, cap, torch.from_numpy(lay["signs"]), torch.from_numpy(lay["rot"]))
+    vd, md = gh.f16dev(v), gh.dev(mod)
+    nd = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    okvq.okvq_append(cache, [0] * B, vd, vd, md, lens, nd, n, flags)
+    codes, norms = torch.zeros_like(cache["v_codes"]), torch.zeros_like(cache["v_norm"])
+    okvq.okvq_quantize_values(cache.dims, vd, md, n, lens, cache.v_rot, flags, codes, norms)
+    torch.cuda.synchronize()
+    assert torch.equal(norms.view(torch.int16), cache["v_norm"].view(torch.int16))
+    assert torch.equal(codes, cache["v_codes"])
