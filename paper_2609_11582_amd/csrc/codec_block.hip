@@ -881,6 +881,21 @@ auto pick(int key_meta, bool ladder) -> void (*)(BlockArgs) {
 
 }  // namespace
 
+// A launch holds fewer than 2^32 threads: beyond, the sequences in two halves (the events around both)
+static hipError_t launch_halves(const BlockArgs& args, int key_meta, bool keys, bool values, int span, hipStream_t s,
+                                hipEvent_t const* events) {
+  if (args.nb < 2) return hipErrorInvalidValue;
+  hipEvent_t ev[2][2] = {{events ? events[0] : nullptr, nullptr}, {nullptr, events ? events[1] : nullptr}};
+  BlockArgs a = args;
+  a.nb = args.nb / 2;
+  const hipError_t e = launch_codec_block(a, key_meta, keys, values, span, s, events ? ev[0] : nullptr);
+  if (e != hipSuccess) return e;
+  a.b0 = args.b0 + args.nb / 2;
+  a.nb = args.nb - args.nb / 2;
+  for (int i = 0; i < a.nb; ++i) a.lens.lens[i] = args.lens.lens[args.nb / 2 + i];
+  return launch_codec_block(a, key_meta, keys, values, span, s, events ? ev[1] : nullptr);
+}
+
 hipError_t launch_codec_block(const BlockArgs& args, int key_meta, bool keys, bool values, int span, hipStream_t s,
                               hipEvent_t const* events) {
   if (args.nb <= 0 || span <= 0 || (!keys && !values)) return hipSuccess;
@@ -891,7 +906,7 @@ hipError_t launch_codec_block(const BlockArgs& args, int key_meta, bool keys, bo
   // beyond, every round of theirs converts R_m again (9216 tokens 16.2 against 13.0, 65536 tokens 46.3 against 35.7).
   const int64_t wide = per * ((span + kWideUnit - 1) / kWideUnit);
   if (!keys && a.key_bits == 0 && !a.rotfrag && wide > 128) {
-    if (wide * 64 * kWideWaves > UINT32_MAX) return hipErrorInvalidValue;  // a launch holds fewer than 2^32 threads
+    if (wide * 64 * kWideWaves > UINT32_MAX) return launch_halves(args, key_meta, keys, values, span, s, events);
     a.val_nx = (span + kWideUnit - 1) / kWideUnit;
     hipLaunchKernelGGL(k_values_wide, dim3((uint32_t)wide), dim3(64 * kWideWaves), 0, s, a);
     return hipGetLastError();
@@ -905,7 +920,7 @@ hipError_t launch_codec_block(const BlockArgs& args, int key_meta, bool keys, bo
   const int val_unit = half_units ? kValUnit / 2 : kValUnit;
   a.val_nx = std::max((span + val_unit - 1) / val_unit, 1);
   const int64_t ku = keys ? per * a.key_nx : 0, vu = values ? per * a.val_nx : 0;
-  if ((ku + vu) * kThreads > UINT32_MAX) return hipErrorInvalidValue;  // a launch holds fewer than 2^32 threads
+  if ((ku + vu) * kThreads > UINT32_MAX) return launch_halves(args, key_meta, keys, values, span, s, events);
   a.key_units = (uint32_t)ku;
   a.paired = (uint32_t)(std::min(ku, vu) / kRun * kRun);
   const bool ladder = a.key_bits != 0;
