@@ -290,9 +290,8 @@ okvq_status okvq_append(const okvq_cache* cache, const int32_t* lens_host, const
  * and values (the window-parallel launch of a small append, or the block codec's), so that
  * hipEventElapsedTime of the pair is that kernel's duration without the host's submission. The cache
  * bytes are those of okvq_append. OKVQ_ERR_INVALID_ARGUMENT for a null events array or handle;
- * OKVQ_ERR_UNSUPPORTED for the bit-width ladder, OKVQ_VALUE_EXACT, the fp16 residual with MXFP4
- * metadata or over more than 64 windows of a sequence or 2048 in all, more than 256 sequences, or no
- * new token, before anything is launched. */
+ * OKVQ_ERR_UNSUPPORTED for the bit-width ladder, OKVQ_VALUE_EXACT, more than 256 sequences, or no new
+ * token, before anything is launched. */
 okvq_status okvq_append_timed(const okvq_cache* cache, const int32_t* lens_host, const uint16_t* k_new,
                               const uint16_t* v_new, const uint8_t* mod_new, const int32_t* n_new_host,
                               const int32_t* n_new_dev, int32_t n_max, uint32_t flags, void* stream,

@@ -224,12 +224,12 @@ void jacobi_eigen(std::vector<double>& a, std::vector<double>& u, std::vector<do
   for (int i = 0; i < n; ++i) d[i] = a[(size_t)i * n + i];
 }
 
-// Appends of at most this many key windows in all (over sequences and KV heads; two work-groups each) take
-// the window-parallel launch, larger ones the block codec and a launch for the lengths. The first has the
-// shorter chain but counts its work-groups one after another, 11.5 ns each. Device time of a call, window
+// Appends of at most this many key windows in all (over sequences and KV heads; a window takes a key and a value
+// work-group) take the window-parallel launch, larger ones the block codec and a launch for the lengths. The first
+// has the shorter chain but counts its work-groups one after another, 11.5 ns each. Device time of a call, window
 // against block: 4 windows (one token, 4 heads) 6.8 / 9.6 us, 128 windows 9.1-9.6 / 9.8-11.4, 256 windows 12.0-13.5
 // / 10.6-11.6, 512 windows 19.7 / 12.8.
-constexpr int64_t kWindowPathMaxGroups = 192;
+constexpr int64_t kWindowPathMaxWindows = 192;
 
 // Tiles of 256 tokens covering `span` tokens from each sequence's first open window (tile codec).
 void plan_tiles(CodecArgs& a, int nb, int span) {
@@ -571,18 +571,15 @@ static okvq_status append_impl(const okvq_cache* cache, const int32_t* lens_host
     const int L = lens_host[b], n = n_new_host[b];
     if (n > 0) nwin = std::max(nwin, (L + n + kW - 1) / kW - L / kW);
   }
-  const int64_t nwg = (int64_t)nwin * d.num_kv_heads * d.batch;
+  const int64_t nwindows = (int64_t)nwin * d.num_kv_heads * d.batch;
   enum { kPathWindow, kPathBlock, kPathTile } path = kPathBlock;
-  if (!exact && nwg <= kWindowPathMaxGroups) path = kPathWindow;
+  if (!exact && nwindows <= kWindowPathMaxWindows) path = kPathWindow;
   if (const char* env = getenv("OKVQ_APPEND_PATH")) {  // force a path (tests, timing)
     if (!strcmp(env, "tile") && !exact) path = kPathTile;
     if (!strcmp(env, "block")) path = kPathBlock;
     if (!strcmp(env, "window") && !exact) path = kPathWindow;
   }
-  // timed appends with the residual rings: those of few windows, in a format other than MXFP4
-  if (events && d.residual &&
-      (path == kPathTile || is_mx(&d) || (nwin > 2 && (nwin > 64 || nwg > 2048) && !getenv("OKVQ_APPEND_PATH"))))
-    return OKVQ_ERR_UNSUPPORTED;
+  if (events && d.residual && path == kPathTile) return OKVQ_ERR_UNSUPPORTED;  // its rings are a second launch
   if (d.residual && span > 0 && (path == kPathTile || exact)) {  // the fp16 rows, before the codec
     if ((int64_t)d.batch * d.num_kv_heads > INT32_MAX) return OKVQ_ERR_UNSUPPORTED;
     st = hip_status(launch_residual_store(k_new, v_new, n_max, cache->seq_lens, n_new_dev, d.batch, d.num_kv_heads,

@@ -109,3 +109,29 @@ def test_timed_append_writes_the_same_bytes(path, plan_name, meta, monkeypatch):
     for name in plain:
         _same(timed[name], plain[name], name)
     assert len(ms) > 0 and all(0.0 < x < 100.0 for x in ms), ms
+
+
+@pytest.mark.parametrize("env", [None, "some other word"])
+@pytest.mark.parametrize("meta,lens,step", [("mxfp4", [300, 40], 100), ("fp16", [2200, 64], 2200), ("mxfp4", [4200], 4200)])
+def test_timed_append_with_residual(meta, lens, step, env, monkeypatch):
+    """The residual rings are filled in the one timed launch, whatever the metadata format, the size (over 64 key
+    windows of a sequence here) or a value of the path variable that names no path: the bytes of okvq_append."""
+    import torch
+
+    import gpu_helpers as gh
+    import paper_2609_11582_amd as okvq
+    _announce(f"timed append, residual {meta} lens={lens} step={step} env={env}")
+    if env:
+        monkeypatch.setenv("OKVQ_APPEND_PATH", env)
+    lay = gen_layer(workload("omni7b_32k"), 5, lengths=np.asarray(lens, np.int32), n_tokens=max(lens))
+    k, v = lay["k"][:, :2].copy(), lay["v"][:, :2].copy()
+    plan = [[max(0, min(step, n - at)) for n in lens] for at in range(0, max(lens), step)]
+    out = []
+    for timed in ([], None):
+        cache = okvq.KVCache(len(lens), 2, 16, -(-max(lens) // 32) * 32, torch.from_numpy(np.asarray(lay["signs"], np.int8)),
+                             torch.from_numpy(np.asarray(lay["rot"], np.float32)), key_meta=meta, residual=128)
+        gh.append_chunks(cache, k, v, lay["modality"], lens, plan, timed=timed)
+        assert timed is None or (len(timed) == len(plan) and all(0.0 < x < 100.0 for x in timed)), timed
+        out.append(gh.cache_to_numpy(cache))
+    for name in out[1]:
+        _same(out[0][name], out[1][name], name)
