@@ -72,3 +72,33 @@ def test_stateless_values_write_the_appended_bytes(lens, heads, flags):
     torch.cuda.synchronize()
     assert torch.equal(norms.view(torch.int16), cache["v_norm"].view(torch.int16))
     assert torch.equal(codes, cache["v_codes"])
+
+
+@pytest.mark.parametrize("meta,kb,vb", [("fp16", 3, 3), ("turboquant", 3, 2), ("fp16", 4, 4), ("turboquant", 2, 4)])
+def test_ladder_append_of_a_long_prompt_writes_the_stateless_bytes(meta, kb, vb):
+    """The ladder's append as a long prompt takes it: keys and values in one launch, at least 256 units of each in
+    alternation, value units of 128 tokens and prepared fragments. Against the stateless calls of the same rows (one
+    role a launch, the fp32 matrix), whose codes the ladder tests compare with the oracle."""
+    import torch
+
+    import paper_2609_11582_amd as okvq
+    B, H, n = 1, 4, 16501
+    g = torch.Generator(device="cuda").manual_seed(10 * kb + vb)
+    k, v = (torch.randn(B, H, n, 128, generator=g, device="cuda").half() for _ in range(2))
+    k[:, :, 77], v[:, :, 33] = 0, 0
+    mod = torch.randint(0, 3, (B, n), generator=g, device="cuda", dtype=torch.uint8)
+    rot = torch.linalg.qr(torch.randn(3, 128, 128, generator=g, device="cuda"))[0].contiguous()
+    print(f"[gpu-case] ladder prompt {meta} K{kb}V{vb}", flush=True)
+    caches = [okvq.KVCache(B, H, H, -(-n // 32) * 32, torch.where(torch.arange(128) % 3 == 0, -1, 1), rot.cpu(),
+                           key_meta=meta, key_bits=kb, value_bits=vb) for _ in range(2)]
+    okvq.okvq_append(caches[0], [0], k, v, mod, [n], torch.tensor([n], dtype=torch.int32, device="cuda"), n)
+    c = caches[1]
+    if meta == "fp16":
+        okvq.okvq_quantize_keys(c.dims, k, n, [n], c.key_signs, c["k_codes"], c["k_min"], c["k_step"], c["k_norm"])
+    else:
+        okvq.okvq_quantize_keys_tq(c.dims, k, n, [n], c.key_signs, c["k_codes"], c["k_norm"])
+    okvq.okvq_quantize_values(c.dims, v, mod, n, [n], c.v_rot, 0, c["v_codes"], c["v_norm"])
+    torch.cuda.synchronize()
+    for name in ("k_codes", "k_norm", "v_codes", "v_norm") + (("k_min", "k_step") if meta == "fp16" else ()):
+        a, b = (x[name].view(torch.uint8) for x in caches)
+        assert torch.equal(a, b), f"{name}: {int((a != b).sum())} bytes differ"
