@@ -51,8 +51,9 @@ constexpr int kATile = 3 * kD + 8;              // fp16 row pitch of the un-rota
 constexpr int kAccPitch = 28;                   // combine tile [channel][24 rows + 4]: conflict-free b128
 constexpr int kMinWps = 2 * kDecWaves;          // fewest windows per split (a pair per wave)
 // Sequences of at most this many windows take one split, whose work-group writes the output rows itself: a
-// second window pair per wave costs less than the merge launch (1024 tokens 11.8 -> 10.4 us, 512 tokens
-// 8.6; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8). Not with the fp16 residual,
+// second window pair per wave costs less than the merge launch (1024 tokens, one split against two: 1 sequence
+// head 10.3 / 10.8 us, 128 heads 10.8 / 11.7, beyond 128 heads two splits no longer fit the compute units at
+// once; at 47 windows the two are equal, at 64 one split takes 14.2 us against 11.8). Not with the fp16 residual,
 // whose tail needs the merge launch anyway: there a second split only helps (4 heads, 1152 tokens, 1024 of
 // them in the splits: 15.8 us with one, 13.6 with two).
 constexpr int kOneSplitWins = 32;
@@ -668,6 +669,18 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
 
   // ---- window pairs through the ring: issue pair k + 2 (if it has tokens), wait for pair k ----
   int hi = issued - 1;  // highest pair issued
+  // The two waves of a SIMD are w and w + 4, and the older one wins every issue: it finished 2-4 us before
+  // the other, which then ran alone. The younger one leads in every second of its rounds, counted from the
+  // last, where the older one leads again: 16 sequences of 16384 tokens and 4 heads with MXFP4 metadata 29.4 ->
+  // 27.1 us, fp16 27.8 -> 25.9, 131072 tokens 19.3 -> 18.9, and 1024 tokens in one split of two rounds 10.5 ->
+  // 10.3. Among several splits not in the last two rounds of two or of an odd number (three: 64 sequence heads of
+  // 5000 tokens with MXFP4 metadata 16.2 -> 15.7 us without; seven: 16 of 50000 tokens 23.55 -> 23.3; four or eight:
+  // 0.1 us more without) and not over TurboQuant keys, whose rounds read no metadata (16 sequence heads of 32768
+  // tokens 18.8 -> 17.8 without). (Younger first in every round: 131072 tokens 19.7, and 32768 tokens 12.4 -> 13.5.)
+  const int total = (w_end - wA0 + 2 * kDecWaves - 1) / (2 * kDecWaves);  // this wave's rounds
+  const int lead_end = (wave < kDecWaves / 2 || (kTq && !kOne)) ? 0
+                       : (kOne || (total > 2 && !(total & 1)))  ? total
+                                                                : total - 2;
   for (int k = 0;; ++k) {
     const int wA = wA0 + 2 * kDecWaves * k;
     if (wA >= w_end) break;
@@ -678,16 +691,7 @@ __global__ __launch_bounds__(64 * kDecWaves) void k_decode(DecodeArgs p) {
       hi = k + 2;
     }
     ring_wait<kMeta>(hi - k);
-    // The two waves of a SIMD are w and w + 4, and the older one wins every issue: it finished 2-4 us before
-    // the other, which then ran alone. The younger one leads in every second of its rounds, counted from the
-    // last, where the older one leads again: 16 sequences of 16384 tokens and 4 heads with MXFP4 metadata 29.4 ->
-    // 27.1 us, fp16 27.8 -> 25.9, 131072 tokens 19.3 -> 18.9, and 1024 tokens in one split of two rounds 10.5 ->
-    // 10.3. Among several splits not where they have three rounds or fewer (64 sequence heads of 5000 tokens with
-    // MXFP4 metadata 16.2 -> 15.7 us without) and not over TurboQuant keys, whose rounds read no metadata (16
-    // sequence heads of 32768 tokens 18.8 -> 17.8 without). (Younger first in every round: 131072 tokens 19.7,
-    // and 32768 tokens 12.4 -> 13.5.)
-    const int rounds = (w_end - wA + 2 * kDecWaves - 1) / (2 * kDecWaves);  // left, with this one
-    if (wave >= kDecWaves / 2 && !(rounds & 1) && (kOne || (!kTq && p.wps > 6 * kDecWaves)))
+    if (k < lead_end && !((k ^ total) & 1))
       __builtin_amdgcn_s_setprio(1);
     else
       __builtin_amdgcn_s_setprio(0);
