@@ -18,8 +18,8 @@ Reported (one JSON line):
                   peak: algorithmic bytes / its mean duration, timed with HIP events bound to its
                   dispatch; traffic = HBM bytes per launch from the committed rocprofv3 counter
                   summary while the kernel sources are unchanged, else null;
-                  roofline_append: the whole append call (the fused codec launch and the length
-                  update)
+                  roofline_append: the whole append call (the codec launch for keys and values and
+                  the launch that advances the lengths), over cold inputs
   kernels_us      mean duration of each launch, from the same events
   codec_split     the prefill's keys and values quantized by separate stateless calls
   cpu_baseline    the CPU oracle on this host: its float64 decode of the same cache on all cores (value)
@@ -87,7 +87,7 @@ PROFILE_COUNTERS = os.path.join(ROOT, "profiles", "hbm_counters.json")
 CALIBRATION_COPY_BYTES = 256 << 20
 KERNEL_SOURCES = ("codec_kernels.hip", "codec_fused.hip", "decode_kernels.hip", "key_quant.hpp", "value_quant.hpp",
                   "okvq_device.hpp", "launch.hpp", "calib_kernels.hip", "dense_decode.hip", "ladder_codec.hip",
-                  "ladder_decode.hip", "append_window.hip", "lane_quant.hpp")
+                  "ladder_decode.hip", "append_window.hip", "lane_quant.hpp", "codec_block.hip", "wave_ops.hpp")
 
 
 def kernel_source_hash() -> str:
@@ -335,7 +335,7 @@ def key_meta_measurement(okvq, torch, np, wl, lens, k_in, v_in, m0, n_new_dev, q
             "decode_GBps": round(dbytes / decode_us / 1e3, 2),
             "k_decode_us": round(split_us, 3), "k_decode_GBps": round(sbytes / split_us / 1e3, 2),
             "k_decode_frac": round(sbytes / split_us / 1e3 / HBM_PEAK_GBPS, 4),
-            "traffic": measured_traffic(f"k_decode_{tag}"), "append_traffic": measured_traffic(f"k_codec_{tag}"),
+            "traffic": measured_traffic(f"k_decode_{tag}"), "append_traffic": measured_traffic(f"k_codec_block_{tag}"),
             "append_us": round(append_us, 3), "append_GBps": round(abytes / append_us / 1e3, 2),
             "append_frac": round(abytes / append_us / 1e3 / HBM_PEAK_GBPS, 4), "algorithmic_bytes": dbytes,
             "replicas": n_cache}
@@ -1188,7 +1188,7 @@ def main():
         "roofline_append": {"bound": "hbm", "achieved": round(append_gbps, 2), "peak": HBM_PEAK_GBPS,
                             "unit": "GB/s", "frac": round(append_gbps / HBM_PEAK_GBPS, 4),
                             "traffic": None,
-                            "kernel": "okvq_append (fused key + value codec launch, length update)",
+                            "kernel": "okvq_append (k_codec_block: keys and values in one launch; k_advance_lengths)",
                             "algorithmic_bytes": abytes},
         "cache_replicas": n_cache,
     }

@@ -26,7 +26,7 @@
  *   status and writes nothing. A failed kernel launch returns OKVQ_ERR_HIP.
  * - Device data contract: inputs are finite and modality ids are 0, 1 or 2. Violations give
  *   unspecified (but memory-safe) results. The one device-side error channel is the cache's
- *   status word (seq_lens[B + 1], read by okvq_cache_status).
+ *   status word (seq_lens[B + 1], read by okvq_cache_status; only the tile codec writes it).
  * - Host "lens" arrays plan the launches; the kernels read lengths on the device where noted.
  *   Callers keep the two equal.
  *
@@ -46,10 +46,12 @@
  *   k_stage  f16 [B][H][32][128]      raw keys of the open (partial) window, used by append
  *   seq_lens i32 [B + 2]              current lengths (device copy), then one word append uses as
  *                                      a work-group counter (zero initially; append leaves it zero),
- *                                      then the status word (zero initially; append sets it to 1 if
- *                                      a wait between the value codec's waves gave up, after which
- *                                      that append's value codes may be wrong; never cleared by
- *                                      the library)
+ *                                      then the status word (zero initially; never cleared by the
+ *                                      library). Only the tile codec sets it, an independent
+ *                                      implementation for comparison that appends take where the
+ *                                      environment variable OKVQ_APPEND_PATH is "tile": to 1 if a
+ *                                      wait between its value waves gave up, after which that
+ *                                      append's value codes may be wrong. No other path has a wait
  * Slots of the last window beyond a sequence's length hold code 0 and norm 0.
  * Storage is 84 bytes per token per KV head: 2.625 bits per element, the "FP16 meta." row of
  * the paper's Tab. 3.
@@ -297,9 +299,10 @@ okvq_status okvq_append_timed(const okvq_cache* cache, const int32_t* lens_host,
                               const int32_t* n_new_dev, int32_t n_max, uint32_t flags, void* stream,
                               void* const* events);
 
-/* Status word of a cache (seq_lens[B + 1]): 0, or 1 once an append's value codec stopped waiting for
- * its partner waves after a bounded number of polls and went on with incomplete tables (that
- * append's value codes may be wrong; addresses stay in bounds). The one call of the library that
+/* Status word of a cache (seq_lens[B + 1]): 0, or 1 once an append on the tile codec
+ * (OKVQ_APPEND_PATH=tile; the other paths never wait and never set it) stopped waiting for a value
+ * wave's partners after a bounded number of polls and went on with incomplete tables (that append's
+ * value codes may be wrong; addresses stay in bounds). The one call of the library that
  * synchronizes: it copies the word to the host after the work already on `stream`.
  *   status  host i32 output
  * OKVQ_ERR_HIP if the copy or the synchronization fails. */
@@ -322,7 +325,9 @@ okvq_status okvq_prepare_rotation(const float* v_rot, uint16_t* v_rot16, void* s
 size_t okvq_decode_workspace_bytes(const okvq_dims* dims, int32_t max_seq_len);
 
 /* One decode step: attention of one query per head over the packed cache (Eq. 1): a split-K
- * launch over windows and a log-sum-exp merge launch.
+ * launch over windows and a log-sum-exp merge launch. Where the plan has one split per sequence (up
+ * to 1024 tokens, 512 in the ladder layout, without the residual) the split launch writes the
+ * outputs itself and there is no merge launch.
  *   lens_host  host i32 [B] (plans the split-K launch; the kernels read cache->seq_lens)
  *   q          device f16 [B][Hq][128]
  *   sm_scale   softmax scale, normally 1/sqrt(128)
@@ -353,10 +358,11 @@ okvq_status okvq_decode_attention(const okvq_cache* cache, const int32_t* lens_h
 okvq_status okvq_decode_attention_noalloc(const okvq_cache* cache, const int32_t* lens_host, const uint16_t* q,
                                           float sm_scale, uint32_t flags, float* out, void* stream);
 
-/* okvq_decode_attention that also times its two launches: events[0] and events[1] are recorded
+/* okvq_decode_attention that also times its launches: events[0] and events[1] are recorded
  * at the start and end of the split-K kernel's execution, events[2] and events[3] at those of
  * the merge kernel (hipEvent_t handles created by the caller; hipEventElapsedTime of a pair is
- * that kernel's duration). */
+ * that kernel's duration). There are always two here: a plan that the untimed call finishes in one
+ * launch is run with its merge, whose rows agree with that call's within the merge's roundings. */
 okvq_status okvq_decode_attention_timed(const okvq_cache* cache, const int32_t* lens_host, const uint16_t* q,
                                         float sm_scale, uint32_t flags, float* out, void* workspace,
                                         size_t workspace_bytes, void* stream, void* const* events);
@@ -385,7 +391,8 @@ size_t okvq_calibration_workspace_bytes(const okvq_dims* dims, int32_t n_tokens)
  *              head h (GQA, j / G = h) and the positions i in [t, lens) of alpha_{i,t}^2; zero for
  *              t >= lens_host[b]
  * Scores on the matrix cores (fp16 operands, fp32 accumulation), softmax statistics and sums in fp32
- * (two launches: row statistics, then column sums). */
+ * (three launches: row statistics, column sums of each query head, the sum over a group's heads).
+ * Attentions below 2^-63 of their row's largest count as zero. A zero scale attends every key alike. */
 okvq_status okvq_calibration_weights(const okvq_dims* dims, const uint16_t* q, const uint16_t* k, int32_t n_tokens,
                                      const int32_t* lens_host, float sm_scale, float* w, void* workspace,
                                      size_t workspace_bytes, void* stream);
@@ -396,7 +403,7 @@ okvq_status okvq_calibration_weights(const okvq_dims* dims, const uint16_t* q, c
  *   cov        device f32 [3][128][128] output: C_m = sum over sequences, KV heads and tokens
  *              t < lens_host[b] of modality m of w_t v_t v_t^T (overwritten, not accumulated)
  * Products on the matrix cores with w v split into fp16 hi + lo parts (about 2^-22 relative per
- * term), fp32 accumulation; per-chunk partials are summed in a fixed order (deterministic). */
+ * term), fp32 accumulation; partials of runs of tokens are summed in a fixed order (deterministic). */
 okvq_status okvq_value_covariance(const okvq_dims* dims, const uint16_t* v, const uint8_t* modality, const float* w,
                                   int32_t n_tokens, const int32_t* lens_host, float* cov, void* workspace,
                                   size_t workspace_bytes, void* stream);

@@ -23,7 +23,7 @@
 // unit, the only one that reads it, rewrites it after a barrier that follows its reads. The lengths
 // advance in a launch of their own: counting finished work-groups on one word costs 11.5 ns each, one
 // after another (8 us of the 39 us of a 32768-token, 4-head prefill with 1024 work-groups), the launch
-// 2.5 us.
+// 1.3-1.6 us.
 //
 // Stateless 2-bit values have no prepared fragments of R_m, only the fp32 matrix, which every work-group converts:
 // large calls take wider units (k_values_wide below).

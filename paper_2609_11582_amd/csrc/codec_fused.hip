@@ -1,8 +1,8 @@
 // Tile codec: key and value codecs of an append in one persistent launch of two waves per SIMD (Sec. 2.1
 // Eq. 2 and Sec. 2.3 Eq. 4 for keys; Sec. 2.3 Eq. 6 with the codebook of Eq. 3 for values). Appends take the
 // block codec (codec_block.hip) or the window-parallel launch (append_window.hip), which are faster at every
-// size measured (32768 tokens, 4 heads: 38.5 us here, 29.9 there); this one runs where OKVQ_APPEND_PATH=tile
-// forces it, as an independent implementation that their bytes are compared with.
+// size measured (32768 tokens, 4 heads: 38.7 us a call here, 29.1 there); this one runs only where
+// OKVQ_APPEND_PATH=tile forces it, as an independent implementation that their bytes are compared with.
 //
 // Work unit: a tile of 256 consecutive tokens of one (sequence, KV head), counted from the
 // sequence's first open window. A work-group has two roles, fixed per wave:

@@ -1047,7 +1047,7 @@ struct TailArgs {
 // average, all of it at multiples of 128 tokens) are bytes for nothing: read as well, they made a call of 512
 // heads at 512 tokens 18.6 us instead of 14.9, and one of 28 heads 13.5 instead of 13.0. Bound by its chain
 // (length, codes, tables, scores, outputs): 28 heads over 64 splits took 6.8 us, 1.45 of it for the scores, 1.2
-// for the groups' two barriers; now 5.5.
+// for the groups' two barriers; now 5.1.
 constexpr int kTabHalf = 68, kTabRow = 2 * kTabHalf;  // table pitches: a wave's broadcast reads hit distinct banks
 
 __global__ __launch_bounds__(kMergeThreads) void k_decode_merge_residual(const float* __restrict__ ws, int H, int Hq,

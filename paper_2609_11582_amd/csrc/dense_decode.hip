@@ -45,7 +45,7 @@ struct DenseArgs {
   const uint16_t* v;        // [B][H][cap][128] fp16
   const int32_t* seq_lens;  // [B]
   const uint16_t* q;        // [B][Hq][128] fp16
-  float* ws;  // partial records; nsplit = 0 (one split per sequence, no merge): the output rows [B][Hq][128]                // split records [B][H][nsplit][kRecFloats]
+  float* ws;                // split records [B][H][nsplit][kRecFloats]; nsplit = 0: the output rows [B][Hq][128]
   int H, Hq, G, cap, tps, nsplit;
   float qscale;             // sm_scale log2(e)
 };
@@ -253,7 +253,8 @@ DensePlan plan_dense(int B, int H, int max_len) {
   const char* env = getenv("OKVQ_DENSE_GROUPS");  // a forced number of groups (tests, timing)
   if (env) target_groups = std::max(1L, atol(env));
   long tps = ((long)max_len * units + target_groups - 1) / target_groups;
-  // one split, without a merge launch, up to two steps: 512 tokens 8.8 -> 7.7 us, 768 tokens 9.5 against 10.2
+  // one split, without a merge launch, up to two steps: 512 tokens 7.8 us against 8.4 (1 sequence head), 8.8 against
+  // 9.9 (128 heads); 768 tokens 10.2 against 9.5
   if (max_len <= 2 * kDnStep && !env) tps = std::max(tps, (long)max_len);
   tps = std::max(tps, (long)kDnStep);
   tps = std::max(tps, ((long)max_len + kMaxSplits - 1) / kMaxSplits);

@@ -668,8 +668,8 @@ LadderPlan plan_ladder(int B, int H, int max_len) {
   const char* env = getenv("OKVQ_LADDER_GROUPS");  // a forced number of groups (tests, timing)
   if (env) target_groups = std::max(1L, atol(env));
   long tps = ((long)max_len * units + target_groups - 1) / target_groups;
-  // one split, without a merge launch, up to two steps: 512 tokens at 4 bits 13.2 -> 12.4 us, 768 tokens
-  // 13.8 against 15.8
+  // one split, without a merge launch, up to two steps: 512 tokens at 4 bits 11.4 us against 11.8 (1 sequence
+  // head), 12.0 against 12.8 (128 heads); 768 tokens 15.8 against 13.8
   if (max_len <= 2 * kLStep && !env) tps = std::max(tps, (long)max_len);
   tps = std::max(tps, (long)kLStep);
   tps = std::max(tps, ((long)max_len + kMaxSplits - 1) / kMaxSplits);
